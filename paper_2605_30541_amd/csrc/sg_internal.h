@@ -126,7 +126,7 @@ struct TileArgs {
     int64_t ring_shot;  // floats per shot in the ring
     // adjoint only
     const float *resid; // [nshot][nrow][nrec], dJ/dd at the recorded levels
-    double *hsum;       // [nshot][frame] sum_n mu^{n+1} (p^{n+1} - 2p^n + p^{n-1}), accumulated in FP64
+    double *hsum;       // [frame] sum over shots and n of mu^{n+1} (p^{n+1} - 2p^n + p^{n-1}), accumulated in FP64
     int32_t nt;
     InjTables inj;
 };
@@ -187,14 +187,14 @@ hipError_t launch_adjoint_tiled_batch(const BatchItem *items, int nitems, int to
 // dst[shot][0..n) = src[shot][0..n) for every shot (strides in floats)
 hipError_t launch_copy(float *dst, int64_t dst_shot, const float *src, int64_t src_shot, int64_t n, int nshot,
                        hipStream_t st);
-// grad[iz][ix] (+)= 2 / (dt^2 v^3) * sum over shots and over the padded cells
-// whose velocity is copied from (iz, ix) of hsum
-// hsum += the adjoint launches' FP32 partial sums kept in ring slots first,
-// first - step, ... (nslot slots), in that order, for every shot of s.
+// hsum[frame] += the adjoint launches' FP32 partial sums kept in ring slots
+// first, first - step, ... (nslot slots) of every shot of s, in that order.
 hipError_t launch_fold_partials(const SliceDesc &s, double *hsum, const float *ring, int64_t ring_shot, int first,
                                 int step, int nslot, hipStream_t st);
-hipError_t launch_fold_gradient(const SliceDesc &s, const float *vp, const double *hsum,
-                                int64_t shot_stride, float dt, float *grad, hipStream_t st, bool accumulate = false);
+// grad[iz][ix] (+)= 2 / (dt^2 v^3) * sum over the padded cells whose velocity
+// is copied from (iz, ix) of hsum
+hipError_t launch_fold_gradient(const SliceDesc &s, const float *vp, const double *hsum, float dt, float *grad,
+                                hipStream_t st, bool accumulate = false);
 // Records level n held in frame `slot` of every shot: gather row (what & 1)
 // and snapshot (what & 2) when that level is due for them.
 hipError_t launch_record_slot(const SliceDesc &s, int n, int slot, hipStream_t st, int what = 3);

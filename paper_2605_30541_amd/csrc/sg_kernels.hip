@@ -754,60 +754,105 @@ __global__ void __launch_bounds__(256) k_copy(float *dst, int64_t dst_shot, cons
         d[i] = sp[i];
 }
 
-// Gradient on the physical grid: g(iz, ix) = 2 / (dt^2 v^3) * sum over shots
-// and over the padded cells whose velocity is the copy of v(iz, ix) (the
-// transpose of the edge replication into the sponge) of h = hsum.
-__global__ void __launch_bounds__(256) k_fold_gradient(SliceDesc s, const float *vp, const double *hsum,
-                                                       int64_t shot_stride, float dt,
-                                                       float *grad, int accumulate)
+// Gradient on the physical grid: g(iz, ix) = 2 / (dt^2 v^3) * sum over the
+// padded cells whose velocity is the copy of v(iz, ix) (the transpose of the
+// edge replication into the sponge) of h = hsum (already summed over shots).
+// Bound: one pass over h.  An interior cell is one thread and one value; an
+// edge cell of the model collects nbl + 1 padded cells (a corner (nbl + 1)^2 =
+// 1681 at a 40-cell sponge), so each edge cell is a wave, its lanes taking the
+// cells in turn and adding up in a fixed tree: one thread per edge cell, and a
+// sum over the shots in each, was a serial chain of 27k dependent additions
+// (2.54 ms for the 620 x 1001 slice with 16 shots; this form 7 us).
+__global__ void __launch_bounds__(256) k_fold_gradient(SliceDesc s, const float *vp, const double *hsum, float dt,
+                                                       float *grad, int accumulate, int inner_blocks)
 {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= s.nz * s.nx) return;
-    const int iz = q / s.nx, ix = q - iz * s.nx;
-    const int z_lo = iz == 0 ? 0 : iz + s.ztop, z_hi = iz == s.nz - 1 ? s.Nz - 1 : iz + s.ztop;
-    const int x_lo = ix == 0 ? 0 : ix + s.xleft, x_hi = ix == s.nx - 1 ? s.Nx - 1 : ix + s.xleft;
+    int iz, ix;
     double acc = 0.0;
-    for (int sh = 0; sh < s.nshot; ++sh) {
-        const double *hs = hsum + (int64_t)sh * shot_stride;
-        for (int Z = z_lo; Z <= z_hi; ++Z)
-            for (int X = x_lo; X <= x_hi; ++X) {
-                const int64_t i = (int64_t)(Z + kGuard) * s.pitch + X + kGuard;
-                acc += hs[i];
-            }
+    const bool edge = (int)blockIdx.x >= inner_blocks;
+    if (!edge) {
+        const int q = blockIdx.x * 256 + threadIdx.x;
+        if (q >= s.nz * s.nx) return;
+        iz = q / s.nx;
+        ix = q - iz * s.nx;
+        if (iz == 0 || iz == s.nz - 1 || ix == 0 || ix == s.nx - 1) return;
+        acc = hsum[(int64_t)(iz + s.ztop + kGuard) * s.pitch + ix + s.xleft + kGuard];
+    } else {
+        // edge cell e: the top row, the bottom row, then the rest of the left
+        // and right columns (each cell once, also where nz or nx is 1)
+        int e = ((int)blockIdx.x - inner_blocks) * 4 + (int)(threadIdx.x >> 6);
+        if (e < s.nx) {
+            iz = 0;
+            ix = e;
+        } else if ((e -= s.nx) < s.nx) {
+            if (s.nz == 1) return;
+            iz = s.nz - 1;
+            ix = e;
+        } else if ((e -= s.nx) < s.nz - 2) {
+            iz = 1 + e;
+            ix = 0;
+        } else if ((e -= max(s.nz - 2, 0)) < s.nz - 2 && s.nx > 1) {
+            iz = 1 + e;
+            ix = s.nx - 1;
+        } else {
+            return;
+        }
+        const int z_lo = iz == 0 ? 0 : iz + s.ztop, z_hi = iz == s.nz - 1 ? s.Nz - 1 : iz + s.ztop;
+        const int x_lo = ix == 0 ? 0 : ix + s.xleft, x_hi = ix == s.nx - 1 ? s.Nx - 1 : ix + s.xleft;
+        const int cols = x_hi - x_lo + 1;
+        const int64_t cells = (int64_t)(z_hi - z_lo + 1) * cols;
+        const int lane = threadIdx.x & 63;
+        for (int64_t c = lane; c < cells; c += 64) {
+            const int Z = z_lo + (int)(c / cols), X = x_lo + (int)(c % cols);
+            acc += hsum[(int64_t)(Z + kGuard) * s.pitch + X + kGuard];
+        }
+        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+        if (lane != 0) return;
     }
+    const int64_t q = (int64_t)iz * s.nx + ix;
     const double v = vp[q];
     const float g = (float)(2.0 / ((double)dt * dt * v * v * v) * acc);
     grad[q] = accumulate ? grad[q] + g : g;
 }
 
-// h += the FP32 partial sums of a segment's adjoint launches, in launch order
-// (slots first, first - step, ...; nslot of them), per padded cell of every
-// shot: the same FP64 additions, in the same order, as adding each launch's
-// partial to h when the launch ends.
+// h += the FP32 partial sums of a segment's adjoint launches, per padded cell:
+// shot after shot, in launch order (slots first, first - step, ...; nslot of
+// them), in FP64.  One accumulator for all shots: only their sum is wanted,
+// so each partial is read once and the accumulator once per segment.
 __global__ void __launch_bounds__(256) k_fold_partials(SliceDesc s, double *hsum, const float *ring, int64_t ring_shot,
                                                        int first, int step, int nslot)
 {
     const int64_t per = (int64_t)s.Nz * s.Nx;
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= per) return;
-    const int shot = blockIdx.y;
     const int Z = (int)(q / s.Nx), X = (int)(q - (int64_t)Z * s.Nx);
     const int64_t i = (int64_t)(Z + kGuard) * s.pitch + X + kGuard;
-    double *h = hsum + (int64_t)shot * s.frame + i;
-    const float *r = ring + (int64_t)shot * ring_shot + i;
-    double acc = *h;
-    // eight slots' loads in flight at a time, added in order
+    double acc = hsum[i];
+    // eight slots' loads in flight at a time, added in order; (sh, j) walks
+    // over the shots' slots
     constexpr int kChunk = 8;
-    for (int j0 = 0; j0 < nslot; j0 += kChunk) {
+    const float *r = ring + i + (int64_t)first * s.frame;
+    const int64_t back = (int64_t)step * s.frame, wrap = ring_shot + (int64_t)(nslot - 1) * back;
+    const int64_t total = (int64_t)s.nshot * nslot;
+    int j = 0;
+    for (int64_t c0 = 0; c0 < total; c0 += kChunk) {
         float v[kChunk];
 #pragma unroll
-        for (int c = 0; c < kChunk; ++c)
-            v[c] = j0 + c < nslot ? r[(int64_t)(first - (j0 + c) * step) * s.frame] : 0.f;
+        for (int c = 0; c < kChunk; ++c) {
+            v[c] = 0.f;
+            if (c0 + c < total) {
+                v[c] = __builtin_nontemporal_load(r);
+                if (++j < nslot) {
+                    r -= back;
+                } else {
+                    j = 0;
+                    r += wrap;
+                }
+            }
+        }
 #pragma unroll
-        for (int c = 0; c < kChunk; ++c)
-            if (j0 + c < nslot) acc += (double)v[c];
+        for (int c = 0; c < kChunk; ++c) acc += (double)v[c];
     }
-    *h = acc;
+    hsum[i] = acc;
 }
 
 __global__ void __launch_bounds__(256) k_count_nonfinite(const float *x, size_t n, unsigned int *count)
@@ -991,12 +1036,13 @@ hipError_t launch_copy(float *dst, int64_t dst_shot, const float *src, int64_t s
     return hipGetLastError();
 }
 
-hipError_t launch_fold_gradient(const SliceDesc &s, const float *vp, const double *hsum,
-                                int64_t shot_stride, float dt, float *grad, hipStream_t st, bool accumulate)
+hipError_t launch_fold_gradient(const SliceDesc &s, const float *vp, const double *hsum, float dt, float *grad,
+                                hipStream_t st, bool accumulate)
 {
-    const unsigned blocks = (unsigned)((s.nz * s.nx + 255) / 256);
-    hipLaunchKernelGGL(k_fold_gradient, dim3(blocks), dim3(256), 0, st, s, vp, hsum, shot_stride, dt, grad,
-                       accumulate ? 1 : 0);
+    const int inner = (int)(((int64_t)s.nz * s.nx + 255) / 256);
+    const int edges = 2 * s.nx + 2 * (s.nz > 2 ? s.nz - 2 : 0);   // cells on the rim, one wave each
+    hipLaunchKernelGGL(k_fold_gradient, dim3((unsigned)(inner + (edges + 3) / 4)), dim3(256), 0, st, s, vp, hsum, dt,
+                       grad, accumulate ? 1 : 0, inner);
     return hipGetLastError();
 }
 
@@ -1005,8 +1051,8 @@ hipError_t launch_fold_partials(const SliceDesc &s, double *hsum, const float *r
 {
     if (nslot <= 0) return hipSuccess;
     const int64_t per = (int64_t)s.Nz * s.Nx;
-    hipLaunchKernelGGL(k_fold_partials, dim3((unsigned)((per + 255) / 256), (unsigned)s.nshot), dim3(256), 0, st, s,
-                       hsum, ring, ring_shot, first, step, nslot);
+    hipLaunchKernelGGL(k_fold_partials, dim3((unsigned)((per + 255) / 256)), dim3(256), 0, st, s, hsum, ring,
+                       ring_shot, first, step, nslot);
     return hipGetLastError();
 }
 

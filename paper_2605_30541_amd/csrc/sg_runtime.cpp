@@ -181,7 +181,7 @@ Layout layout_of(const sg_plan *p, int nshot, int nrec, int ckpt = 0)
         L.ring = take((size_t)nshot * L.ring_levels * fr);
         L.ring2 = take((size_t)nshot * L.ring_levels * fr);   // segments alternate between the two rings
         L.mu = take((size_t)nshot * sg::kFramesPerShot * fr);
-        L.hsum = take((size_t)nshot * 2 * fr);     // doubles
+        L.hsum = take((size_t)nshot * 2 * fr);     // doubles (one frame, summed over the shots, is used)
     }
     L.total = o;
     return L;
@@ -1371,7 +1371,7 @@ sg_status sg_adjoint_gradient(sg_plan *p, const float *vp, const sg_shots *shots
     double *hsum = (double *)(w + c.L.hsum);
     const int64_t ck_shot = (int64_t)c.L.nseg * 2 * F, ring_shot = (int64_t)c.L.ring_levels * F;
     SG_HIP(sg::launch_zero(mu, (size_t)nshot * fshot, st));
-    SG_HIP(sg::launch_zero((float *)hsum, (size_t)nshot * 2 * F, st));
+    SG_HIP(sg::launch_zero((float *)hsum, (size_t)2 * F, st));
 
     sg::InjTables inj{};
     inj.tile_start = (const int32_t *)(w + c.L.inj_tile);
@@ -1430,7 +1430,7 @@ sg_status sg_adjoint_gradient(sg_plan *p, const float *vp, const sg_shots *shots
     }
     // every fold is done (they run in order on the side stream)
     SG_HIP(hipStreamWaitEvent(st, p->ev_fold[0], 0));
-    SG_HIP(sg::launch_fold_gradient(s, vp, hsum, F, (float)p->g.dt, grad, st));
+    SG_HIP(sg::launch_fold_gradient(s, vp, hsum, (float)p->g.dt, grad, st));
     return SG_OK;
 }
 
@@ -1779,7 +1779,7 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             const int64_t F = it.plan->frame;
             SG_HIP(sg::launch_zero(b.s.fields, (size_t)cnt * sg::kFramesPerShot * F, st));
             SG_HIP(sg::launch_zero((float *)(wi + L.mu), (size_t)cnt * sg::kFramesPerShot * F, st));
-            SG_HIP(sg::launch_zero((float *)(wi + L.hsum), (size_t)cnt * 2 * F, st));
+            SG_HIP(sg::launch_zero((float *)(wi + L.hsum), (size_t)2 * F, st));
             b.t = tile_args(Tf[i], b.s.fields, 0, 0, 0);
             b.t.ring = (float *)(wi + L.ring);
             b.t.ring_shot = (int64_t)L.ring_levels * F;
@@ -1934,8 +1934,8 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
         SG_HIP(hipStreamWaitEvent(st, p0->ev_fold[0], 0));
         for (int q = 0; q < na; ++q) {
             const sg_batch_grad_item &it = items[act[q]];
-            SG_HIP(sg::launch_fold_gradient(hb[q].s, it.vp, hb[q].t.hsum, it.plan->frame,
-                                            (float)it.plan->g.dt, it.grad, st, wv > 0));
+            SG_HIP(sg::launch_fold_gradient(hb[q].s, it.vp, hb[q].t.hsum, (float)it.plan->g.dt, it.grad, st,
+                                            wv > 0));
         }
     }
     return SG_OK;
