@@ -116,8 +116,14 @@ struct TileArgs {
     int32_t tx, tz;     // output tile
     int32_t tz_top;     // output rows of the top tile row under a free top
     int32_t ntx, ntz;   // tiles per row / column
-    int32_t in_pair, out_pair;
+    // the two levels read and the two written: frames of the older and the
+    // newer level, in_shot / out_shot floats from one shot to the next
+    const float *in;
+    float *out;
+    int64_t in_shot, out_shot;
     float *fields;      // [nshot][kFramesPerShot][frame]
+    float *ck;          // batched gradient: checkpoint j of a shot is ck + j * 2 frames, ck_shot floats per shot
+    int64_t ck_shot;
     // forward with ring != null: the second time difference D^n of the output
     // tile is stored in ring slot n - ring_lo for every level n advanced;
     // adjoint: the ring holds D^ring_lo .. D^ring_hi read by the imaging term
@@ -130,6 +136,21 @@ struct TileArgs {
     int32_t nt;
     InjTables inj;
 };
+
+// Where a batched launch reads and writes its levels: the field pair in_pair
+// and the other one, or, where in_ck / out_ck >= 0, that checkpoint.
+struct LevelPair {
+    int32_t in_pair;
+    int32_t in_ck = -1, out_ck = -1;
+};
+__host__ __device__ inline void set_levels(TileArgs &t, int64_t frame, const LevelPair &lv)
+{
+    t.in = lv.in_ck >= 0 ? t.ck + (int64_t)(2 * lv.in_ck) * frame : t.fields + (int64_t)(2 * lv.in_pair) * frame;
+    t.in_shot = lv.in_ck >= 0 ? t.ck_shot : kFramesPerShot * frame;
+    t.out = lv.out_ck >= 0 ? t.ck + (int64_t)(2 * lv.out_ck) * frame
+                           : t.fields + (int64_t)(2 * (lv.in_pair ^ 1)) * frame;
+    t.out_shot = lv.out_ck >= 0 ? t.ck_shot : kFramesPerShot * frame;
+}
 
 // One slice of a batched launch: its descriptor, its tiling and field
 // pointers (launch-level fields of `t` are overwritten per launch), and the
@@ -174,19 +195,20 @@ hipError_t launch_adjoint_tiled(const SliceDesc &s, const TileArgs &t, int confi
 // form) also the second time differences into the ring, as the tiled kernel's
 // recompute mode.  The batched form like launch_step_tiled_batch.
 hipError_t launch_sweep(const SliceDesc &s, const TileArgs &t, int nw, hipStream_t st);
-hipError_t launch_sweep_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps, int in_pair,
-                              int nw, hipStream_t st, bool ring = false, int ring_lo = 0);
+hipError_t launch_sweep_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
+                              LevelPair lv, int nw, hipStream_t st, bool ring = false, int ring_lo = 0);
 // Batched launches: items[0..nitems) in device memory, total_blocks = sum of
 // the items' blocks (items[i].block_start is the prefix sum).
 hipError_t launch_step_tiled_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
-                                   int in_pair, int config, bool iso, hipStream_t st);
+                                   LevelPair lv, int config, bool iso, hipStream_t st);
 hipError_t launch_ring_tiled_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
-                                   int in_pair, int config, bool iso, int ring_lo, hipStream_t st);
+                                   LevelPair lv, int config, bool iso, int ring_lo, hipStream_t st);
 hipError_t launch_adjoint_tiled_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
-                                      int in_pair, int config, bool iso, int ring_lo, int ring_hi, hipStream_t st);
-// dst[shot][0..n) = src[shot][0..n) for every shot (strides in floats)
-hipError_t launch_copy(float *dst, int64_t dst_shot, const float *src, int64_t src_shot, int64_t n, int nshot,
-                       hipStream_t st);
+                                   LevelPair lv, int config, bool iso, int ring_lo, int ring_hi, hipStream_t st);
+// Checkpoints of every shot (nseg pairs of frames each, ck_shot floats per
+// shot): the cells outside the padded grid set to 0, and the whole of pair 0
+// (levels -1 and 0).
+hipError_t launch_init_checkpoints(const SliceDesc &s, float *ck, int64_t ck_shot, int nseg, hipStream_t st);
 // hsum[frame] += the adjoint launches' FP32 partial sums kept in ring slots
 // first, first - step, ... (nslot slots) of every shot of s, in that order.
 hipError_t launch_fold_partials(const SliceDesc &s, double *hsum, const float *ring, int64_t ring_shot, int first,
@@ -195,8 +217,11 @@ hipError_t launch_fold_partials(const SliceDesc &s, double *hsum, const float *r
 // is copied from (iz, ix) of hsum
 hipError_t launch_fold_gradient(const SliceDesc &s, const float *vp, const double *hsum, float dt, float *grad,
                                 hipStream_t st, bool accumulate = false);
-// Records level n held in frame `slot` of every shot: gather row (what & 1)
-// and snapshot (what & 2) when that level is due for them.
+// Records level n held in `level` (frame of shot 0; shot_stride floats per
+// shot): gather row (what & 1) and snapshot (what & 2) when that level is due
+// for them.  The second form takes frame `slot` of every shot's fields.
+hipError_t launch_record(const SliceDesc &s, int n, const float *level, int64_t shot_stride, hipStream_t st,
+                         int what = 3);
 hipError_t launch_record_slot(const SliceDesc &s, int n, int slot, hipStream_t st, int what = 3);
 hipError_t launch_count_nonfinite(const float *x, size_t n, unsigned int *count, hipStream_t st);
 

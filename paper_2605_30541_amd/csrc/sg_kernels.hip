@@ -15,6 +15,7 @@
 // overwrites level n-1 with level n+1 in place.
 #include "sg_internal.h"
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -156,12 +157,12 @@ __global__ void __launch_bounds__(256) k_step_naive(SliceDesc s, int n)
     nxt[i] = v;
 }
 
-// Records level n held in frame `slot` of every shot: the gather row when
+// Records level n held in a frame of every shot: the gather row when
 // (what & 1), the snapshot when (what & 2), each only if that level is due.
-__global__ void __launch_bounds__(256) k_record(SliceDesc s, int n, int slot, int what)
+__global__ void __launch_bounds__(256) k_record(SliceDesc s, int n, const float *level, int64_t shot_stride, int what)
 {
     const int shot = blockIdx.y;
-    const float *cur = s.fields + ((int64_t)shot * kFramesPerShot + slot) * s.frame;
+    const float *cur = level + (int64_t)shot * shot_stride;
     if (!(what & 1)) s.gathers = nullptr;
     if (!(what & 2)) s.snaps = nullptr;
     record_level(s, cur, shot, n, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
@@ -313,10 +314,9 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
     const bool seg_dead = Z0 >= s.Nz || Z0 + K <= 0 || wave_x0 >= s.Nx || wave_x0 + 64 <= 0;
     const bool ghost_writer = top_tile && Z0 <= kHalo && Z0 + K > 1;
 
-    const int64_t fshot = (int64_t)shot * kFramesPerShot * s.frame;
-    const float *in_prev = t.fields + fshot + (int64_t)(2 * t.in_pair) * s.frame;
+    const float *in_prev = t.in + (int64_t)shot * t.in_shot;
     const float *in_cur = in_prev + s.frame;
-    float *out_prev = t.fields + fshot + (int64_t)(2 * t.out_pair) * s.frame;
+    float *out_prev = t.out + (int64_t)shot * t.out_shot;
     float *out_cur = out_prev + s.frame;
     // byte offset in a stored field of (row Z0 + k, column X): a uniform row
     // part rowb(k) plus the lane's column part xo4 (xc4 at the clamped column)
@@ -715,7 +715,7 @@ __global__ void __launch_bounds__(64 * NWX * NWZ) SG_TILED_OCCUPANCY k_tiled(Sli
 // launch-level fields (levels, pairs) come from the arguments.
 template <int K, int NWX, int NWZ, int MODE, bool ISO>
 __global__ void __launch_bounds__(64 * NWX * NWZ) SG_TILED_OCCUPANCY k_tiled_batch(const BatchItem *__restrict__ items, int nitems,
-                                                                 int n, int nsteps, int in_pair, int ring_lo, int ring_hi)
+                                                                 int n, int nsteps, LevelPair lv, int ring_lo, int ring_hi)
 {
     __shared__ float lds[2 * TileShape<K, NWX, NWZ>::LDS];
     const int b = xcd_remap(blockIdx.x, gridDim.x);
@@ -737,21 +737,23 @@ __global__ void __launch_bounds__(64 * NWX * NWZ) SG_TILED_OCCUPANCY k_tiled_bat
     TileArgs t = items[it].t;
     t.n = n;
     t.nsteps = nsteps;
-    t.in_pair = in_pair;
-    t.out_pair = in_pair ^ 1;
+    set_levels(t, s.frame, lv);
     t.ring_lo = ring_lo;
     t.ring_hi = ring_hi;
     tiled_body<K, NWX, NWZ, MODE, ISO>(s, t, b - items[it].block_start, lds);
 }
 
-__global__ void __launch_bounds__(256) k_copy(float *dst, int64_t dst_shot, const float *src, int64_t src_shot,
-                                              int64_t n)
+// Guard cells (and row padding) of every checkpoint frame to 0, and the whole
+// of pair 0.  The launches write only padded-grid cells, and read guards.
+__global__ void __launch_bounds__(256) k_init_checkpoints(SliceDesc s, int frame0, float *ck, int64_t ck_shot)
 {
-    const int shot = blockIdx.y;
-    float *d = dst + (int64_t)shot * dst_shot;
-    const float *sp = src + (int64_t)shot * src_shot;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        d[i] = sp[i];
+    const int fr = frame0 + blockIdx.y, shot = blockIdx.z;
+    float *p = ck + (int64_t)shot * ck_shot + (int64_t)fr * s.frame;
+    for (int64_t r = blockIdx.x; r < s.Nz + 2 * kGuard; r += gridDim.x) {
+        const bool all = fr < 2 || r < kGuard || r >= s.Nz + kGuard;
+        for (int c = threadIdx.x; c < s.pitch; c += 256)
+            if (all || c < kGuard || c >= s.Nx + kGuard) p[r * s.pitch + c] = 0.f;
+    }
 }
 
 // Gradient on the physical grid: g(iz, ix) = 2 / (dt^2 v^3) * sum over the
@@ -889,14 +891,19 @@ hipError_t launch_step_naive(const SliceDesc &s, int n, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_record_slot(const SliceDesc &s, int n, int slot, hipStream_t st, int what)
+hipError_t launch_record(const SliceDesc &s, int n, const float *level, int64_t shot_stride, hipStream_t st, int what)
 {
     int work = s.nrec;
     if (s.snaps && s.nz * s.nx > work) work = s.nz * s.nx;
     unsigned blocks = (unsigned)((work + 255) / 256);
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_record, dim3(blocks, s.nshot), dim3(256), 0, st, s, n, slot, what);
+    hipLaunchKernelGGL(k_record, dim3(blocks, s.nshot), dim3(256), 0, st, s, n, level, shot_stride, what);
     return hipGetLastError();
+}
+
+hipError_t launch_record_slot(const SliceDesc &s, int n, int slot, hipStream_t st, int what)
+{
+    return launch_record(s, n, s.fields + (int64_t)slot * s.frame, kFramesPerShot * s.frame, st, what);
 }
 
 namespace {
@@ -929,12 +936,12 @@ Tiling make_tiling(int Nz, int Nx, bool free_top, int ex, int ez, int k, int tb)
 // are equal, one weight per m) and the general form.
 template <int MODE, bool ISO>
 static hipError_t launch_tiled_batch_iso(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
-                                         int in_pair, int config, int ring_lo, int ring_hi, hipStream_t st)
+                                   LevelPair lv, int config, int ring_lo, int ring_hi, hipStream_t st)
 {
     const dim3 g((unsigned)total_blocks);
 #define SG_BATCH_LAUNCH(KK, NX, NZ, THR)                                                                    \
     hipLaunchKernelGGL((k_tiled_batch<KK, NX, NZ, MODE, ISO>), g, dim3(THR), 0, st, items, nitems, n, nsteps, \
-                       in_pair, ring_lo, ring_hi)
+                       lv, ring_lo, ring_hi)
     switch (config) {
     case 0: SG_BATCH_LAUNCH(8, 2, 8, 1024); break;
     case 1: SG_BATCH_LAUNCH(16, 1, 8, 512); break;
@@ -947,25 +954,25 @@ static hipError_t launch_tiled_batch_iso(const BatchItem *items, int nitems, int
 }
 
 hipError_t launch_step_tiled_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
-                                   int in_pair, int config, bool iso, hipStream_t st)
+                                   LevelPair lv, int config, bool iso, hipStream_t st)
 {
-    return iso ? launch_tiled_batch_iso<kFwd, true>(items, nitems, total_blocks, n, nsteps, in_pair, config, 0, 0, st)
-               : launch_tiled_batch_iso<kFwd, false>(items, nitems, total_blocks, n, nsteps, in_pair, config, 0, 0, st);
+    return iso ? launch_tiled_batch_iso<kFwd, true>(items, nitems, total_blocks, n, nsteps, lv, config, 0, 0, st)
+               : launch_tiled_batch_iso<kFwd, false>(items, nitems, total_blocks, n, nsteps, lv, config, 0, 0, st);
 }
 
 hipError_t launch_ring_tiled_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
-                                   int in_pair, int config, bool iso, int ring_lo, hipStream_t st)
+                                   LevelPair lv, int config, bool iso, int ring_lo, hipStream_t st)
 {
-    return iso ? launch_tiled_batch_iso<kRing, true>(items, nitems, total_blocks, n, nsteps, in_pair, config, ring_lo, 0, st)
-               : launch_tiled_batch_iso<kRing, false>(items, nitems, total_blocks, n, nsteps, in_pair, config, ring_lo, 0, st);
+    return iso ? launch_tiled_batch_iso<kRing, true>(items, nitems, total_blocks, n, nsteps, lv, config, ring_lo, 0, st)
+               : launch_tiled_batch_iso<kRing, false>(items, nitems, total_blocks, n, nsteps, lv, config, ring_lo, 0, st);
 }
 
 hipError_t launch_adjoint_tiled_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
-                                      int in_pair, int config, bool iso, int ring_lo, int ring_hi, hipStream_t st)
+                                   LevelPair lv, int config, bool iso, int ring_lo, int ring_hi, hipStream_t st)
 {
-    return iso ? launch_tiled_batch_iso<kAdj, true>(items, nitems, total_blocks, n, nsteps, in_pair, config, ring_lo,
+    return iso ? launch_tiled_batch_iso<kAdj, true>(items, nitems, total_blocks, n, nsteps, lv, config, ring_lo,
                                                     ring_hi, st)
-               : launch_tiled_batch_iso<kAdj, false>(items, nitems, total_blocks, n, nsteps, in_pair, config, ring_lo,
+               : launch_tiled_batch_iso<kAdj, false>(items, nitems, total_blocks, n, nsteps, lv, config, ring_lo,
                                                      ring_hi, st);
 }
 
@@ -1026,13 +1033,16 @@ hipError_t launch_adjoint_tiled(const SliceDesc &s, const TileArgs &t, int confi
     return isotropic(s) ? launch_tiled<kAdj, true>(s, t, config, st) : launch_tiled<kAdj, false>(s, t, config, st);
 }
 
-hipError_t launch_copy(float *dst, int64_t dst_shot, const float *src, int64_t src_shot, int64_t n, int nshot,
-                       hipStream_t st)
+hipError_t launch_init_checkpoints(const SliceDesc &s, float *ck, int64_t ck_shot, int nseg, hipStream_t st)
 {
-    if (n <= 0 || nshot <= 0) return hipSuccess;
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_copy, dim3((unsigned)blocks, nshot), dim3(256), 0, st, dst, dst_shot, src, src_shot, n);
+    // (grid y and z extents are limited to 65535)
+    constexpr int kMost = 32768;
+    for (int f0 = 0; f0 < 2 * nseg; f0 += kMost)
+        for (int s0 = 0; s0 < s.nshot; s0 += kMost) {
+            const dim3 grid(8, (unsigned)std::min(kMost, 2 * nseg - f0), (unsigned)std::min(kMost, s.nshot - s0));
+            hipLaunchKernelGGL(k_init_checkpoints, grid, dim3(256), 0, st, s, f0,
+                               ck + (int64_t)s0 * ck_shot, ck_shot);
+        }
     return hipGetLastError();
 }
 

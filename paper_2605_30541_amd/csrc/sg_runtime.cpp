@@ -557,7 +557,7 @@ sg_status prof_pair(sg_plan *p, int i, hipEvent_t *a, hipEvent_t *b)
     return SG_OK;
 }
 
-sg::TileArgs tile_args(const sg::Tiling &T, float *fields, int n, int nsteps, int in_pair)
+sg::TileArgs tile_args(const sg::Tiling &T, float *fields, int64_t frame, int n, int nsteps, int in_pair)
 {
     sg::TileArgs a{};
     a.n = n;
@@ -568,21 +568,28 @@ sg::TileArgs tile_args(const sg::Tiling &T, float *fields, int n, int nsteps, in
     a.tz_top = T.tz_top;
     a.ntx = T.ntx;
     a.ntz = T.ntz;
-    a.in_pair = in_pair;
-    a.out_pair = in_pair ^ 1;
     a.fields = fields;
+    sg::set_levels(a, frame, sg::LevelPair{in_pair});
     return a;
 }
 
 // Forward launches from level n0 to level n_end on the field pairs of `s`
 // (`*pair` holds levels n0-1, n0 on entry and n_end-1, n_end on return).
-// Launches end at every multiple of `cut` (if > 0) so the caller can act on
-// those levels through on_cut(level, pair).  With a ring, every new level is
-// also stored there.  With profiling on, one event pair brackets the run.
-template <class OnCut>
+// With a ring, every new level is also stored there.  With checkpoints (`ck`)
+// the run starts from the one at level n0; when they are saved, launches end
+// at every multiple of their spacing and write those two levels straight into
+// the checkpoint, from which the next launch reads them (a copy of the pair
+// after such a launch, and back before a recompute, was 3.6 % of the 16-shot
+// gradient).  With profiling on, one event pair brackets the run.
+struct Checkpoints {
+    float *base;       // checkpoint j of a shot: 2 frames at base + 2 j frames (levels j every - 1, j every)
+    int64_t shot;      // floats per shot
+    int every;
+    bool save;
+};
 sg_status forward_run(sg_plan *p, const sg::SliceDesc &s, const sg_tuning &t, int config, const sg::Tiling &T,
-                      int n0, int n_end, int cut, int *pair, float *ring, int ring_lo, int64_t ring_shot,
-                      OnCut on_cut, hipStream_t st, int *count = nullptr)
+                      int n0, int n_end, int *pair, float *ring, int ring_lo, int64_t ring_shot,
+                      const Checkpoints *ck, hipStream_t st, int *count = nullptr)
 {
     const int step = t.variant == 1 ? 1 : t.time_block;
     // the tiled kernel leaves snapshots to launch boundaries at snapshot levels
@@ -599,13 +606,21 @@ sg_status forward_run(sg_plan *p, const sg::SliceDesc &s, const sg_tuning &t, in
     int launches = 0;
     for (int n = n0; n < n_end; ++launches) {
         int k = std::min(step, n_end - n);
-        if (cut > 0) k = std::min(k, cut - n % cut);
+        if (ck && ck->save) k = std::min(k, ck->every - n % ck->every);
         if (snap_cuts && n < slast) k = std::min(k, se - n % se);
         if (t.variant == 1) {
             SG_HIP(sg::launch_step_naive(s, n, st));
             *pair = 0;
         } else {
-            sg::TileArgs a = tile_args(T, s.fields, n, k, *pair);
+            sg::TileArgs a = tile_args(T, s.fields, s.frame, n, k, *pair);
+            if (ck) {
+                a.ck = ck->base;
+                a.ck_shot = ck->shot;
+                sg::LevelPair lv{*pair};
+                if (n == n0 || (ck->save && n % ck->every == 0)) lv.in_ck = n / ck->every;
+                if (ck->save && (n + k) % ck->every == 0) lv.out_ck = (n + k) / ck->every;
+                sg::set_levels(a, s.frame, lv);
+            }
             a.ring = ring;
             a.ring_lo = ring_lo;
             a.ring_shot = ring_shot;
@@ -618,10 +633,6 @@ sg_status forward_run(sg_plan *p, const sg::SliceDesc &s, const sg_tuning &t, in
         }
         n += k;
         if (n < n_end && snap_due(n)) SG_HIP(sg::launch_record_slot(s, n, 2 * (*pair) + 1, st, 2));
-        if (cut > 0 && n % cut == 0) {
-            sg_status rc = on_cut(n, *pair);
-            if (rc != SG_OK) return rc;
-        }
     }
     if (p->profiling) {
         SG_HIP(hipEventRecord(e1, st));
@@ -838,8 +849,7 @@ sg_status run_forward(sg_plan *p, const sg::SliceDesc &s, const sg_tuning &t, in
     int launches = 0;
     auto enqueue = [&](hipStream_t s2) -> sg_status {
         int pair = 0;
-        sg_status rc = forward_run(p, s, t, config, T, 0, nt - 1, 0, &pair, nullptr, 0, 0,
-                                   [](int, int) { return SG_OK; }, s2, &launches);
+        sg_status rc = forward_run(p, s, t, config, T, 0, nt - 1, &pair, nullptr, 0, 0, nullptr, s2, &launches);
         if (rc != SG_OK) return rc;
         SG_HIP(sg::launch_record_slot(s, nt - 1, level_slot(t, nt - 1, pair), s2));
         return SG_OK;
@@ -1333,20 +1343,17 @@ sg_status sg_forward_ckpt(sg_plan *p, const float *vp, const sg_shots *shots, in
     float *ck = (float *)(w + c.L.ckpt);
     const int64_t ck_shot = (int64_t)c.L.nseg * 2 * p->frame;
     // checkpoint 0 holds levels -1 and 0, both zero
-    SG_HIP(sg::launch_copy(ck, ck_shot, s.fields, (int64_t)sg::kFramesPerShot * p->frame, 2 * p->frame, nshot, st));
+    SG_HIP(sg::launch_init_checkpoints(s, ck, ck_shot, c.L.nseg, st));
     int pair = 0;
     p->prof_used = 0;
-    auto on_cut = [&](int level, int pr) -> sg_status {
-        const int j = level / C;
-        if (j >= c.L.nseg) return SG_OK;
-        // levels level-1, level are frames 2 pr, 2 pr + 1 of the pair
-        SG_HIP(sg::launch_copy(ck + (int64_t)j * 2 * p->frame, ck_shot, s.fields + (int64_t)(2 * pr) * p->frame,
-                               (int64_t)sg::kFramesPerShot * p->frame, 2 * p->frame, nshot, st));
-        return SG_OK;
-    };
-    rc = forward_run(p, s, c.tf, c.config_f, c.Tf, 0, nt - 1, C, &pair, nullptr, 0, 0, on_cut, st);
+    const Checkpoints cks{ck, ck_shot, C, true};
+    rc = forward_run(p, s, c.tf, c.config_f, c.Tf, 0, nt - 1, &pair, nullptr, 0, 0, &cks, st);
     if (rc != SG_OK) return rc;
-    SG_HIP(sg::launch_record_slot(s, nt - 1, level_slot(c.tf, nt - 1, pair), st));
+    // the last level is in the last checkpoint or in the field pair
+    if ((nt - 1) % C == 0)
+        SG_HIP(sg::launch_record(s, nt - 1, ck + (int64_t)(2 * ((nt - 1) / C) + 1) * p->frame, ck_shot, st));
+    else
+        SG_HIP(sg::launch_record_slot(s, nt - 1, level_slot(c.tf, nt - 1, pair), st));
     return SG_OK;
 }
 
@@ -1393,12 +1400,10 @@ sg_status sg_adjoint_gradient(sg_plan *p, const float *vp, const sg_shots *shots
         if (folding[j & 1]) SG_HIP(hipStreamWaitEvent(st, p->ev_fold[j & 1], 0));
         // recompute levels lo+1 .. last from checkpoint j (levels lo-1, lo),
         // storing D^lo .. D^{last-1} in the ring
-        const float *ckj = ck + (int64_t)j * 2 * F;
-        SG_HIP(sg::launch_copy(s.fields, fshot, ckj, ck_shot, 2 * F, nshot, st));
         int pair = 0;
         if (last > lo) {
-            rc = forward_run(p, s, c.tf, c.config_f, c.Tf, lo, last, 0, &pair, ring, lo, ring_shot,
-                             [](int, int) { return SG_OK; }, st);
+            const Checkpoints cks{ck, ck_shot, C, false};
+            rc = forward_run(p, s, c.tf, c.config_f, c.Tf, lo, last, &pair, ring, lo, ring_shot, &cks, st);
             if (rc != SG_OK) return rc;
         }
         // adjoint steps k = hi .. lo (mu^k from mu^{k+1}, mu^{k+2}) with imaging;
@@ -1407,7 +1412,7 @@ sg_status sg_adjoint_gradient(sg_plan *p, const float *vp, const sg_shots *shots
         for (int k0 = hi; k0 >= lo;) {
             ++nlaunch;
             const int nsteps = std::min(c.t.time_block, k0 - lo + 1);
-            sg::TileArgs a = tile_args(c.T, mu, k0, nsteps, mpair);
+            sg::TileArgs a = tile_args(c.T, mu, F, k0, nsteps, mpair);
             a.ring = ring;
             a.ring_lo = lo;
             a.ring_hi = last - 1;
@@ -1496,7 +1501,7 @@ sg_status batch_forward_impl(const sg_batch_item *items, int32_t nitems, const s
         hb[i].s = describe(it.plan, cs[i].L, wi, it.shots, trial ? nullptr : it.gathers, trial ? nullptr : it.snaps);
         SG_HIP(sg::launch_prepare(hb[i].s, it.vp, (float)(it.plan->g.dt * it.plan->g.dt), st));
         SG_HIP(sg::launch_zero(hb[i].s.fields, (size_t)it.shots->nshot * sg::kFramesPerShot * it.plan->frame, st));
-        hb[i].t = tile_args(cs[i].T, hb[i].s.fields, 0, 0, 0);
+        hb[i].t = tile_args(cs[i].T, hb[i].s.fields, hb[i].s.frame, 0, 0, 0);
         hb[i].block_start = start;
         start += cs[i].T.ntx * cs[i].T.ntz * it.shots->nshot;
     }
@@ -1534,9 +1539,9 @@ sg_status batch_forward_impl(const sg_batch_item *items, int32_t nitems, const s
         for (int n = 0; n < nlast;) {
             const int k = std::min(std::min(tb, nlast - n), next_cut(n) - n);
             if (sweep_nw > 0)
-                SG_HIP(sg::launch_sweep_batch(dev_items, nitems, (int)total_blocks, n, k, pair, sweep_nw, s2));
+                SG_HIP(sg::launch_sweep_batch(dev_items, nitems, (int)total_blocks, n, k, {pair}, sweep_nw, s2));
             else
-                SG_HIP(sg::launch_step_tiled_batch(dev_items, nitems, (int)total_blocks, n, k, pair, config, iso, s2));
+                SG_HIP(sg::launch_step_tiled_batch(dev_items, nitems, (int)total_blocks, n, k, {pair}, config, iso, s2));
             pair ^= 1;
             n += k;
             if (n < nlast)
@@ -1655,8 +1660,7 @@ sg_status sg_autotune(sg_plan *p, const float *vp, const sg_shots *shots, int32_
         for (int rep = 0; rep < 2 && rc == SG_OK; ++rep) {
             if (rep == 1 && hipEventRecord(e0, st) != hipSuccess) rc = fail(SG_EHIP, "event record failed");
             if (rc == SG_OK)
-                rc = forward_run(p, s, t, config, T, 0, levels, 0, &pair, nullptr, 0, 0,
-                                 [](int, int) { return SG_OK; }, st);
+                rc = forward_run(p, s, t, config, T, 0, levels, &pair, nullptr, 0, 0, nullptr, st);
             if (rep == 1 && rc == SG_OK && hipEventRecord(e1, st) != hipSuccess) rc = fail(SG_EHIP, "event record failed");
         }
         p->profiling = prof;
@@ -1780,7 +1784,9 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             SG_HIP(sg::launch_zero(b.s.fields, (size_t)cnt * sg::kFramesPerShot * F, st));
             SG_HIP(sg::launch_zero((float *)(wi + L.mu), (size_t)cnt * sg::kFramesPerShot * F, st));
             SG_HIP(sg::launch_zero((float *)(wi + L.hsum), (size_t)2 * F, st));
-            b.t = tile_args(Tf[i], b.s.fields, 0, 0, 0);
+            b.t = tile_args(Tf[i], b.s.fields, F, 0, 0, 0);
+            b.t.ck = (float *)(wi + L.ckpt);
+            b.t.ck_shot = (int64_t)L.nseg * 2 * F;
             b.t.ring = (float *)(wi + L.ring);
             b.t.ring_shot = (int64_t)L.ring_levels * F;
             b.t.resid = it.resid + (size_t)s0 * it.plan->nrow * it.shots->nrec;
@@ -1799,7 +1805,7 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             // the adjoint's entry: its tiling, fields in the adjoint pair
             sg::BatchItem ba = b;
             const sg::TileArgs keep_t = b.t;
-            ba.t = tile_args(T[i], (float *)(wi + L.mu), 0, 0, 0);
+            ba.t = tile_args(T[i], (float *)(wi + L.mu), F, 0, 0, 0);
             ba.t.ring = keep_t.ring;
             ba.t.ring_shot = keep_t.ring_shot;
             ba.t.resid = keep_t.resid;
@@ -1810,8 +1816,7 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             start_adj += T[i].ntx * T[i].ntz * cnt;
             hb_adj.push_back(ba);
             // checkpoint 0: levels -1 and 0, both zero
-            SG_HIP(sg::launch_copy((float *)(wi + L.ckpt), (int64_t)L.nseg * 2 * F, b.s.fields,
-                                   (int64_t)sg::kFramesPerShot * F, 2 * F, cnt, st));
+            SG_HIP(sg::launch_init_checkpoints(b.s, b.t.ck, b.t.ck_shot, L.nseg, st));
         }
         const int na = (int)act.size();
         // two device copies of the item table (forward fields, adjoint fields),
@@ -1840,43 +1845,20 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             if ((rc = stage_upload(dev_fwd_r[0], all.data(), 4 * tbl, st)) != SG_OK) return rc;
         }
         sg::BatchItem *const dev_fwd = dev_fwd_r[0];
-        auto copy_items = [&](auto dst_of, auto src_of, int64_t n) -> sg_status {
-            for (int q = 0; q < na; ++q) {
-                const int64_t F = items[act[q]].plan->frame;
-                float *dst;
-                int64_t dshot;
-                const float *src;
-                int64_t sshot;
-                dst_of(q, F, &dst, &dshot);
-                src_of(q, F, &src, &sshot);
-                SG_HIP(sg::launch_copy(dst, dshot, src, sshot, n * F, views[q].nshot, st));
-            }
-            return SG_OK;
-        };
-        // forward with checkpoints (no outputs)
+        // forward with checkpoints (no outputs): launches end at every
+        // checkpoint level and write it in place, where the next one reads it
         int pair = 0;
         for (int n = 0; n < nt - 1;) {
             const int k = std::min(std::min(tf.time_block, nt - 1 - n), C - n % C);
+            sg::LevelPair lv{pair};
+            if (n % C == 0) lv.in_ck = n / C;
+            if ((n + k) % C == 0) lv.out_ck = (n + k) / C;
             if (sweep_fwd)
-                SG_HIP(sg::launch_sweep_batch(dev_fwd, na, start, n, k, pair, Tf[0].sweep_nw, st));
+                SG_HIP(sg::launch_sweep_batch(dev_fwd, na, start, n, k, lv, Tf[0].sweep_nw, st));
             else
-                SG_HIP(sg::launch_step_tiled_batch(dev_fwd, na, start, n, k, pair, config, iso, st));
+                SG_HIP(sg::launch_step_tiled_batch(dev_fwd, na, start, n, k, lv, config, iso, st));
             pair ^= 1;
             n += k;
-            if (n % C == 0 && n / C < Ls[0].nseg) {
-                const int j = n / C, pr = pair;
-                rc = copy_items(
-                    [&](int q, int64_t F, float **d, int64_t *ds) {
-                        *d = (float *)((char *)hb[q].s.fields - Ls[q].fields + Ls[q].ckpt) + (int64_t)j * 2 * F;
-                        *ds = (int64_t)Ls[q].nseg * 2 * F;
-                    },
-                    [&](int q, int64_t F, const float **sp, int64_t *ss) {
-                        *sp = hb[q].s.fields + (int64_t)(2 * pr) * F;
-                        *ss = (int64_t)sg::kFramesPerShot * F;
-                    },
-                    2);
-                if (rc != SG_OK) return rc;
-            }
         }
         // segments backwards: recompute into the segment's ring, then the
         // adjoint; its partial sums are folded on the side stream while the
@@ -1890,24 +1872,15 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             const int lo = j * C, hi = std::min((j + 1) * C - 1, nt - 1), last = std::min(hi + 1, nt - 1);
             const int rb = j & 1;
             if (folding[rb]) SG_HIP(hipStreamWaitEvent(st, p0->ev_fold[rb], 0));
-            rc = copy_items(
-                [&](int q, int64_t F, float **d, int64_t *ds) {
-                    *d = hb[q].s.fields;
-                    *ds = (int64_t)sg::kFramesPerShot * F;
-                },
-                [&](int q, int64_t F, const float **sp, int64_t *ss) {
-                    *sp = (const float *)((char *)hb[q].s.fields - Ls[q].fields + Ls[q].ckpt) + (int64_t)j * 2 * F;
-                    *ss = (int64_t)Ls[q].nseg * 2 * F;
-                },
-                2);
-            if (rc != SG_OK) return rc;
             int fp = 0;
             for (int n = lo; n < last;) {
                 const int k = std::min(tf.time_block, last - n);
+                sg::LevelPair lv{fp};
+                if (n == lo) lv.in_ck = j;
                 if (sweep_fwd)
-                    SG_HIP(sg::launch_sweep_batch(dev_fwd_r[rb], na, start, n, k, fp, Tf[0].sweep_nw, st, true, lo));
+                    SG_HIP(sg::launch_sweep_batch(dev_fwd_r[rb], na, start, n, k, lv, Tf[0].sweep_nw, st, true, lo));
                 else
-                    SG_HIP(sg::launch_ring_tiled_batch(dev_fwd_r[rb], na, start, n, k, fp, config, iso, lo, st));
+                    SG_HIP(sg::launch_ring_tiled_batch(dev_fwd_r[rb], na, start, n, k, lv, config, iso, lo, st));
                 fp ^= 1;
                 n += k;
             }
@@ -1915,7 +1888,7 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             for (int k0 = hi; k0 >= lo;) {
                 ++nlaunch;
                 const int ns = std::min(t.time_block, k0 - lo + 1);
-                SG_HIP(sg::launch_adjoint_tiled_batch(dev_adj_r[rb], na, start_adj, k0, ns, mpair, config, iso, lo,
+                SG_HIP(sg::launch_adjoint_tiled_batch(dev_adj_r[rb], na, start_adj, k0, ns, {mpair}, config, iso, lo,
                                                       last - 1, st));
                 mpair ^= 1;
                 k0 -= ns;

@@ -87,10 +87,9 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
         R = min(max(R, -kGuard), Nz + kGuard - 1);
         return (uint32_t)((R + kGuard) * pitch) * 4u;
     };
-    const int64_t fshot = (int64_t)shot * kFramesPerShot * s.frame;
-    const float *in_prev = t.fields + fshot + (int64_t)(2 * t.in_pair) * s.frame;
+    const float *in_prev = t.in + (int64_t)shot * t.in_shot;
     const float *in_cur = in_prev + s.frame;
-    float *out_prev = t.fields + fshot + (int64_t)(2 * t.out_pair) * s.frame;
+    float *out_prev = t.out + (int64_t)shot * t.out_shot;
     float *out_cur = out_prev + s.frame;
     const bool free_top = s.free_top != 0;
 
@@ -286,7 +285,7 @@ __global__ void __launch_bounds__(64 * NW) k_sweep(SliceDesc s, TileArgs t)
 
 template <int NW, int TB, bool RECOMP>
 __global__ void __launch_bounds__(64 * NW) k_sweep_batch(const BatchItem *__restrict__ items, int nitems, int n,
-                                                          int in_pair, int ring_lo)
+                                                          LevelPair lv, int ring_lo)
 {
     __shared__ float lds[TB * kQ * (64 * NW + 2 * kHalo)];
     const int b = xcd_block(blockIdx.x, gridDim.x);
@@ -305,21 +304,20 @@ __global__ void __launch_bounds__(64 * NW) k_sweep_batch(const BatchItem *__rest
     TileArgs t = items[it].t;
     t.n = n;
     t.nsteps = TB;
-    t.in_pair = in_pair;
-    t.out_pair = in_pair ^ 1;
+    set_levels(t, s.frame, lv);
     t.ring_lo = ring_lo;
     sweep_body<NW, TB, RECOMP>(s, t, b - items[it].block_start, lds);
 }
 
 template <int NW, bool RECOMP>
 hipError_t launch_sweep_nw(const SliceDesc *s, const TileArgs *t, const BatchItem *items, int nitems,
-                           unsigned blocks, int n, int nsteps, int in_pair, int ring_lo, hipStream_t st)
+                           unsigned blocks, int n, int nsteps, LevelPair lv, int ring_lo, hipStream_t st)
 {
 #define SG_SWEEP(TBV)                                                                                                \
     case TBV:                                                                                                        \
         if (items)                                                                                                   \
             hipLaunchKernelGGL((k_sweep_batch<NW, TBV, RECOMP>), dim3(blocks), dim3(64 * NW), 0, st, items, nitems, \
-                               n, in_pair, ring_lo);                                                                 \
+                               n, lv, ring_lo);                                                                      \
         else                                                                                                         \
             hipLaunchKernelGGL((k_sweep<NW, TBV, RECOMP>), dim3(blocks), dim3(64 * NW), 0, st, *s, *t);            \
         break
@@ -361,23 +359,23 @@ hipError_t launch_sweep(const SliceDesc &s, const TileArgs &t, int nw, hipStream
     const unsigned blocks = (unsigned)(t.ntx * t.ntz * s.nshot);
     const bool ring = t.ring != nullptr;
     switch (nw * 2 + (ring ? 1 : 0)) {
-    case 4: return launch_sweep_nw<2, false>(&s, &t, nullptr, 0, blocks, t.n, t.nsteps, t.in_pair, 0, st);
-    case 5: return launch_sweep_nw<2, true>(&s, &t, nullptr, 0, blocks, t.n, t.nsteps, t.in_pair, 0, st);
-    case 8: return launch_sweep_nw<4, false>(&s, &t, nullptr, 0, blocks, t.n, t.nsteps, t.in_pair, 0, st);
-    case 9: return launch_sweep_nw<4, true>(&s, &t, nullptr, 0, blocks, t.n, t.nsteps, t.in_pair, 0, st);
+    case 4: return launch_sweep_nw<2, false>(&s, &t, nullptr, 0, blocks, t.n, t.nsteps, {}, 0, st);
+    case 5: return launch_sweep_nw<2, true>(&s, &t, nullptr, 0, blocks, t.n, t.nsteps, {}, 0, st);
+    case 8: return launch_sweep_nw<4, false>(&s, &t, nullptr, 0, blocks, t.n, t.nsteps, {}, 0, st);
+    case 9: return launch_sweep_nw<4, true>(&s, &t, nullptr, 0, blocks, t.n, t.nsteps, {}, 0, st);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_sweep_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps, int in_pair,
-                              int nw, hipStream_t st, bool ring, int ring_lo)
+hipError_t launch_sweep_batch(const BatchItem *items, int nitems, int total_blocks, int n, int nsteps,
+                              LevelPair lv, int nw, hipStream_t st, bool ring, int ring_lo)
 {
     const unsigned b = (unsigned)total_blocks;
     switch (nw * 2 + (ring ? 1 : 0)) {
-    case 4: return launch_sweep_nw<2, false>(nullptr, nullptr, items, nitems, b, n, nsteps, in_pair, 0, st);
-    case 5: return launch_sweep_nw<2, true>(nullptr, nullptr, items, nitems, b, n, nsteps, in_pair, ring_lo, st);
-    case 8: return launch_sweep_nw<4, false>(nullptr, nullptr, items, nitems, b, n, nsteps, in_pair, 0, st);
-    case 9: return launch_sweep_nw<4, true>(nullptr, nullptr, items, nitems, b, n, nsteps, in_pair, ring_lo, st);
+    case 4: return launch_sweep_nw<2, false>(nullptr, nullptr, items, nitems, b, n, nsteps, lv, 0, st);
+    case 5: return launch_sweep_nw<2, true>(nullptr, nullptr, items, nitems, b, n, nsteps, lv, ring_lo, st);
+    case 8: return launch_sweep_nw<4, false>(nullptr, nullptr, items, nitems, b, n, nsteps, lv, 0, st);
+    case 9: return launch_sweep_nw<4, true>(nullptr, nullptr, items, nitems, b, n, nsteps, lv, ring_lo, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -2,7 +2,9 @@
 FP64 oracle (relative L2 <= 1e-4, the bar of every propagation test): the fold
 of the padded cells onto the edge cells of the model (models of one or two
 rows or columns, no sponge, a sponge wider than the model, both tops, more
-shots than one)."""
+shots than one), and checkpoints written in place (the last level on a
+checkpoint, one past it, a checkpoint at every level, a spacing longer than
+the record)."""
 import numpy as np
 import pytest
 
@@ -39,3 +41,10 @@ def run_case(nz, nx, nbl, top, nt, ckpt, nshot=3, tuning=None):
     (33, 65, 40, sgwave.SG_TOP_FREE), (3, 3, 1, sgwave.SG_TOP_FREE)])
 def test_fold_onto_the_edge_cells(nz, nx, nbl, top):
     run_case(nz, nx, nbl, top, nt=40, ckpt=9)
+
+
+@pytest.mark.parametrize("tuning", [None, dict(variant=3, tile_x=128, tile_z=0, time_block=4)],
+                         ids=["tiled", "sweep"])
+@pytest.mark.parametrize("nt,ckpt", [(41, 10), (42, 10), (40, 10), (30, 1), (30, 64), (25, 24), (3, 2)])
+def test_checkpoints_in_place(nt, ckpt, tuning):
+    run_case(21, 37, 6, sgwave.SG_TOP_FREE, nt=max(nt, 3), ckpt=ckpt, tuning=tuning)
