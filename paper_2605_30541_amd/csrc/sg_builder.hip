@@ -32,7 +32,7 @@ constexpr int kTaps = 8;
 typedef float Float4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr float kBeta = 6.f;
 constexpr int kBrickZ = 16, kBrickY = 16, kBrickRows = kBrickZ * kBrickY;   // fault kernel
-constexpr int kDepositThreads = 64;   // one wave per workgroup; its contacts fill up to 64 KB of LDS
+constexpr int kDepositThreads = 256;   // 64 columns, four waves; the contacts fill up to 64 KB of LDS
 
 // Normalised weights of the taps floor(s)-3 .. floor(s)+4 for the fractional
 // part f = s - floor(s): tap j sits at t = f + 3 - j from the sample and
@@ -422,71 +422,87 @@ __global__ void __launch_bounds__(256) k_fault_labels(const int32_t *__restrict_
     out[q] = lab[(int64_t)jz * plane + (int64_t)jy * nx + jx];
 }
 
+// a / b rounded as IEEE division rounds it, y = 1 / b rounded: the quotient
+// estimate is corrected twice by its exact remainder, the second correction of
+// an estimate within one unit in the last place (Markstein's theorem: the
+// result is then the correctly rounded quotient).  Five operations instead of
+// the full division's dozen; a, b and the quotient within 2^+-900 or a = 0.
+__device__ inline double div_by(double a, double b, double y)
+{
+    double q = a * y;
+    q = fma(fma(-b, q, a), y, q);
+    return fma(fma(-b, q, a), y, q);
+}
+
+// f mod 256 of an integer-valued f as an index
+__device__ inline int mod256(double f) { return (int)(f - 256.0 * floor(f * 0.00390625)) & 255; }
+
 // 3D simplex noise (Perlin's simplex noise as formulated by Gustavson,
 // "Simplex noise demystified", 2005), FP64, at lattice coordinates (a, b, c):
 // skew by 1/3 onto the cubic lattice, pick the tetrahedron of the cube cell
 // by the order of the unskewed offsets, and add over its four corners
 // (0.6 - |d|^2)^4 (g . d) where positive, g the cube-edge midpoint chosen by
 // the corner's hash P[i + P[j + P[k]]] mod 12 (indices mod 256); times 32.
-// P: 256 entries in 0..255 (LDS).  With the published radius 0.6 a corner's
-// kernel reaches past the faces of its tetrahedron, so the field jumps
-// slightly across them; which tetrahedron a point on a face takes is decided
-// by IEEE operations without fusion (a sum, a division, floor, differences),
-// the same decision as any IEEE evaluation of the same coordinates.
-__device__ inline double simplex_corner(const int *P, int i, int j, int k, double x, double y, double z)
+// With the published radius 0.6 a corner's kernel reaches past the faces of
+// its tetrahedron, so the field jumps slightly across them; which tetrahedron
+// a point on a face takes is decided by IEEE operations without fusion (a sum,
+// a division, floor, differences), the same decision as any IEEE evaluation of
+// the same coordinates.
+//
+// Bound by vector issue, so there is no branch: neighbouring lanes differ in
+// hash, and a switch over the twelve gradients ran up to twelve times per
+// corner.  The gradients are two of the three offsets with signs; P (LDS, 256
+// words) carries which, beside the permutation in the low byte.
+constexpr int kGradY = 1 << 8, kGradZ = 1 << 9, kSignU = 1 << 30;   // (sign of the second: bit 31)
+
+// The word of a permutation entry: hash h = p mod 12 picks g . d = u + v with u
+// = x (h < 8) or y, v = y (h < 4) or z, u negated when h is odd, v when h & 2.
+__device__ inline int simplex_word(int p)
+{
+    const int h = p % 12;
+    return p | (h >= 8 ? kGradY : 0) | (h >= 4 ? kGradZ : 0) | (h & 1 ? kSignU : 0) | (int)((unsigned)(h & 2) << 30);
+}
+
+__device__ inline double flip_sign(double v, unsigned sign_bit)
+{
+    return __hiloint2double(__double2hiint(v) ^ (int)sign_bit, __double2loint(v));
+}
+
+__device__ inline double simplex_corner(int word, double x, double y, double z)
 {
     const double w = 0.6 - (x * x + y * y + z * z);
-    if (!(w > 0.0)) return 0.0;
-    const int h = P[(i + P[(j + P[k & 255]) & 255]) & 255] % 12;
-    double dot;
-    switch (h) {
-    case 0: dot = x + y; break;
-    case 1: dot = -x + y; break;
-    case 2: dot = x - y; break;
-    case 3: dot = -x - y; break;
-    case 4: dot = x + z; break;
-    case 5: dot = -x + z; break;
-    case 6: dot = x - z; break;
-    case 7: dot = -x - z; break;
-    case 8: dot = y + z; break;
-    case 9: dot = -y + z; break;
-    case 10: dot = y - z; break;
-    default: dot = -y - z; break;
-    }
+    const double u = flip_sign(word & kGradY ? y : x, ((unsigned)word << 1) & 0x80000000u);
+    const double v = flip_sign(word & kGradZ ? z : y, (unsigned)word & 0x80000000u);
     const double w2 = w * w;
-    return w2 * w2 * dot;
+    return w > 0.0 ? w2 * w2 * (u + v) : 0.0;
 }
 
 __device__ inline double simplex3(const int *P, double a, double b, double c)
 {
-    const double s = (a + b + c) / 3.0;
+    const double s = div_by(a + b + c, 3.0, 1.0 / 3.0);
     const double fi = floor(a + s), fj = floor(b + s), fk = floor(c + s);
-    const double t = (fi + fj + fk) / 6.0;
+    const double t = div_by(fi + fj + fk, 6.0, 1.0 / 6.0);
     const double x0 = a - (fi - t), y0 = b - (fj - t), z0 = c - (fk - t);
     // corners 1 and 2 step along the largest, then the two largest offsets
     // (ties: the lower axis first)
-    int i1, j1, k1, i2, j2, k2;
-    if (x0 >= y0) {
-        if (y0 >= z0) { i1 = 1; j1 = 0; k1 = 0; i2 = 1; j2 = 1; k2 = 0; }
-        else if (x0 >= z0) { i1 = 1; j1 = 0; k1 = 0; i2 = 1; j2 = 0; k2 = 1; }
-        else { i1 = 0; j1 = 0; k1 = 1; i2 = 1; j2 = 0; k2 = 1; }
-    } else {
-        if (y0 < z0) { i1 = 0; j1 = 0; k1 = 1; i2 = 0; j2 = 1; k2 = 1; }
-        else if (x0 < z0) { i1 = 0; j1 = 1; k1 = 0; i2 = 0; j2 = 1; k2 = 1; }
-        else { i1 = 0; j1 = 1; k1 = 0; i2 = 1; j2 = 1; k2 = 0; }
-    }
-    const int i = (int)(int64_t)fi & 255, j = (int)(int64_t)fj & 255, k = (int)(int64_t)fk & 255;
-    double n = simplex_corner(P, i, j, k, x0, y0, z0);
-    n += simplex_corner(P, i + i1, j + j1, k + k1, x0 - i1 + 1.0 / 6.0, y0 - j1 + 1.0 / 6.0, z0 - k1 + 1.0 / 6.0);
-    n += simplex_corner(P, i + i2, j + j2, k + k2, x0 - i2 + 2.0 / 6.0, y0 - j2 + 2.0 / 6.0, z0 - k2 + 2.0 / 6.0);
-    n += simplex_corner(P, i + 1, j + 1, k + 1, x0 - 1.0 + 0.5, y0 - 1.0 + 0.5, z0 - 1.0 + 0.5);
+    const bool xy = x0 >= y0, xz = x0 >= z0, yz = y0 >= z0;
+    const bool i1 = xy && xz, j1 = !xy && yz, k1 = !xz && !yz;
+    const bool i2 = xy || xz, j2 = !xy || yz, k2 = !xz || !yz;
+    const int i = mod256(fi), j = mod256(fj), k = mod256(fk);
+    const int p0 = P[k], p1 = P[(k + 1) & 255];
+    auto word = [&](int di, int dj, bool dk) { return P[(i + di + P[(j + dj + (dk ? p1 : p0)) & 255]) & 255]; };
+    auto less = [](double v, bool d) { return v - (d ? 1.0 : 0.0); };
+    double n = simplex_corner(word(0, 0, false), x0, y0, z0);
+    n += simplex_corner(word(i1, j1, k1), less(x0, i1) + 1.0 / 6.0, less(y0, j1) + 1.0 / 6.0, less(z0, k1) + 1.0 / 6.0);
+    n += simplex_corner(word(i2, j2, k2), less(x0, i2) + 2.0 / 6.0, less(y0, j2) + 2.0 / 6.0, less(z0, k2) + 2.0 / 6.0);
+    n += simplex_corner(word(1, 1, true), x0 - 1.0 + 0.5, y0 - 1.0 + 0.5, z0 - 1.0 + 0.5);
     return 32.0 * n;
 }
 
-// A permutation table into LDS (entries taken mod 256); all threads call it.
+// The words of a permutation table into LDS (entries taken mod 256); all threads call it.
 __device__ inline void load_perm(const int32_t *perm, int *P)
 {
-    for (int q = threadIdx.x; q < 256; q += blockDim.x) P[q] = perm[q] & 255;
+    for (int q = threadIdx.x; q < 256; q += blockDim.x) P[q] = simplex_word(perm[q] & 255);
     __syncthreads();
 }
 
@@ -513,28 +529,34 @@ __global__ void __launch_bounds__(256) k_simplex3d(const int32_t *__restrict__ p
     }
 }
 
-// Deposit (Alg. 1, boundary path): one thread per (y, x) column, walking down
-// the band [t][ny][nx].  The contacts are the cumulative bed thicknesses
-// (summed in FP64 in bed order), each moved by taper x a_B x its noise and
-// clamped to the band; they are computed once per column into LDS (FP64,
-// [contact][lane]), and at every depth the voxel's bed is the number of
-// contacts at or above it, starting at the deepest of those; the texture is
-// sampled at the depth below that start plus the bed's offset.  SIMPLEX: the
-// contact noise is simplex noise (perm_b) on the plane at the contact's mean
-// depth and the texture simplex noise (perm_t); else the contact noise is an
-// input and the texture value noise on a lattice.
+// Deposit (Alg. 1, boundary path): a workgroup takes 64 (y, x) columns of the
+// band [t][ny][nx] and a run of its depths, each of its waves a quarter of the
+// run.  The contacts are the cumulative bed thicknesses (summed in FP64 in bed
+// order), each moved by taper x a_B x its noise and clamped to the band; the
+// waves compute them into LDS (FP64, [contact][lane]) in turn, and one wave
+// sorts each column's (they are nearly in order).  A voxel's bed is the
+// number of contacts at or above it, starting at the deepest of those, so
+// walking down only looks at the next contact; the texture is sampled at the
+// depth below that start plus the bed's offset.  SIMPLEX: the contact noise is
+// simplex noise (perm_b) on the plane at the contact's mean depth and the
+// texture simplex noise (perm_t); else the contact noise is an input and the
+// texture value noise on a lattice.
+// Bound by FP64 vector issue (about 200 operations a voxel with simplex
+// texture).  One thread per whole column, all contacts looked at for every
+// voxel, left two waves per SIMD (LDS) and took 7.29 ms for a 200 x 1000 x
+// 1000 band of 40 beds with simplex noise; this form 1.47 ms.
 template <bool SIMPLEX>
-__global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, float *__restrict__ out)
+__global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, int run, float *__restrict__ out)
 {
-    extern __shared__ double hcol[];   // [nbeds - 1][kDepositThreads]
+    extern __shared__ double hcol[];   // [nbeds - 1][64]
     __shared__ int Pb[SIMPLEX ? 256 : 1], Pt[SIMPLEX ? 256 : 1];
     if (SIMPLEX) {
         load_perm(A.perm_b, Pb);
         load_perm(A.perm_t, Pt);
     }
     const int64_t plane = (int64_t)A.ny * A.nx;
-    const int64_t col = (int64_t)blockIdx.x * kDepositThreads + threadIdx.x;
-    if (col >= plane) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t col0 = (int64_t)blockIdx.x * 64 + lane, col = min(col0, plane - 1);
     const int iy = (int)(col / A.nx), ix = (int)(col - (int64_t)iy * A.nx);
     const double t = A.t;
     // taper min(d / (f_top t), 1) min((t - d) / (f_base t), 1), by reciprocals
@@ -547,13 +569,14 @@ __global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, floa
     auto fade = [](double u) { return u * u * u * (u * (u * 6.0 - 15.0) + 10.0); };
     auto wrap = [](double f, int g) { const int64_t i = (int64_t)f % g; return (int)(i < 0 ? i + g : i); };
     auto L = [&](int a, int b, int c) { return (double)A.lattice[((int64_t)a * A.gy + b) * A.gx + c]; };
-    double ty = 0.0, tx = 0.0, by = 0.0, bx = 0.0;
+    double ty = 0.0, tx = 0.0, by = 0.0, bx = 0.0, rlam = 0.0;
     int y0 = 0, x0 = 0, y1 = 0, x1 = 0;
     if (SIMPLEX) {
         ty = iy * A.dy / A.lam_t[1];
         tx = ix * A.dx / A.lam_t[2];
         by = iy * A.dy / A.lam_b[1];
         bx = ix * A.dx / A.lam_b[2];
+        rlam = 1.0 / A.lam_t[0];
     } else {
         const double py = iy * A.dy * A.inv_lam_y, px = ix * A.dx * A.inv_lam_x;
         const double fy = floor(py), fx = floor(px);
@@ -564,25 +587,48 @@ __global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, floa
         y1 = (y0 + 1) % A.gy;
         x1 = (x0 + 1) % A.gx;
     }
+    const int nc = A.nbeds - 1;
     {
         double H = 0.0;
-        for (int i = 0; i + 1 < A.nbeds; ++i) {
+        for (int i = 0; i < nc; ++i) {
             H += (double)A.thick[i];
+            if (i % (kDepositThreads / 64) != wv) continue;
             const double eta =
                 SIMPLEX ? simplex3(Pb, H * A.dz / A.lam_b[0], by, bx) : (double)A.eta_b[(int64_t)i * plane + col];
-            hcol[i * kDepositThreads + threadIdx.x] = fmin(fmax(H + tau(H) * A.a_B * eta, 0.0), t - 1.0);
+            hcol[i * 64 + lane] = fmin(fmax(H + tau(H) * A.a_B * eta, 0.0), t - 1.0);
         }
     }
-    for (int iz = 0; iz < A.t; ++iz) {
-        const double z = iz;
-        int bed = 0;
-        double start = 0.0;
-        for (int i = 0; i + 1 < A.nbeds; ++i) {
-            const double h = hcol[i * kDepositThreads + threadIdx.x];
-            if (h <= z) {
-                ++bed;
-                start = fmax(start, h);
+    __syncthreads();
+    if (wv == 0)
+        for (int i = 1; i < nc; ++i) {   // insertion sort, ascending
+            const double h = hcol[i * 64 + lane];
+            int q = i;
+            for (; q > 0; --q) {
+                const double g = hcol[(q - 1) * 64 + lane];
+                if (g <= h) break;
+                hcol[q * 64 + lane] = g;
             }
+            if (q < i) hcol[q * 64 + lane] = h;
+        }
+    __syncthreads();
+    if (col0 >= plane) return;
+    const int b0 = (int)blockIdx.y * run, b1 = min(A.t, b0 + run);   // the workgroup's depths
+    const int part = (b1 - b0 + kDepositThreads / 64 - 1) / (kDepositThreads / 64);
+    const int z0w = b0 + wv * part, z1w = min(b1, z0w + part);
+    const double none = INFINITY;   // (no further contact)
+    int bed = 0;
+    double start = 0.0, next = nc > 0 ? hcol[lane] : none;
+    double off = (double)A.tex_off[0], dv = (double)A.vbed[0] - vbar;
+    for (int iz = z0w; iz < z1w; ++iz) {
+        const double z = iz;
+        if (next <= z) {
+            do {
+                start = next;
+                ++bed;
+                next = bed < nc ? hcol[bed * 64 + lane] : none;
+            } while (next <= z);
+            off = (double)A.tex_off[bed];
+            dv = (double)A.vbed[bed] - vbar;
         }
         // texture at ((z - start) dz + offset, y dy, x dx)
         double eta;
@@ -591,11 +637,12 @@ __global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, floa
             double zt;
             {
 #pragma clang fp contract(off)
-                zt = ((z - start) * A.dz + (double)A.tex_off[bed]) / A.lam_t[0];
+                zt = (z - start) * A.dz + off;
             }
+            zt = A.exact_div ? zt / A.lam_t[0] : div_by(zt, A.lam_t[0], rlam);
             eta = simplex3(Pt, zt, ty, tx);
         } else {
-            const double pz = ((z - start) * A.dz + (double)A.tex_off[bed]) * A.inv_lam_z;
+            const double pz = ((z - start) * A.dz + off) * A.inv_lam_z;
             const double fz = floor(pz);
             const double tz = fade(pz - fz);
             const int z0 = wrap(fz, A.gz), z1 = (z0 + 1) % A.gz;
@@ -605,7 +652,7 @@ __global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, floa
                         ty * ((1 - tx) * L(z1, y1, x0) + tx * L(z1, y1, x1)));
         }
         out[(int64_t)iz * plane + col] =
-            (float)((vbar + A.beta * z * A.dz) + tau(z) * (((double)A.vbed[bed] - vbar) + A.a_eta * eta));
+            (float)((vbar + A.beta * z * A.dz) + tau(z) * (dv + A.a_eta * eta));
     }
 }
 
@@ -702,13 +749,22 @@ __global__ void __launch_bounds__(kSinThreads) k_deposit_sin(DepositSinArgs A, f
 hipError_t launch_deposit(const DepositArgs &A, float *out, hipStream_t st)
 {
     if (A.nbeds < 1 || A.nbeds > kDepositMaxBeds) return hipErrorInvalidValue;
-    const int64_t n = (int64_t)A.ny * A.nx;
-    const size_t lds = (size_t)std::max(A.nbeds - 1, 1) * kDepositThreads * sizeof(double);
-    const dim3 grid((unsigned)((n + kDepositThreads - 1) / kDepositThreads));
+    const int64_t n = (int64_t)A.ny * A.nx, cols = (n + 63) / 64;
+    const size_t lds = (size_t)std::max(A.nbeds - 1, 1) * 64 * sizeof(double);
+    // A small area leaves the chip idle with one workgroup per 64 columns:
+    // the depths are then cut in runs (each repeats the columns' contacts)
+    // until there are 1024 workgroups or a run is 16 depths.
+    int run = A.t;
+    while (run > 16 && cols * ((A.t + run - 1) / run) < 1024) run = (run + 1) / 2;
+    const dim3 grid((unsigned)cols, (unsigned)((A.t + run - 1) / run));
+    DepositArgs B = A;
+    // div_by takes lengths and depths far from the ends of the FP64 range
+    const double big = 0x1p200, lam = A.lam_t[0];
+    B.exact_div = A.simplex && !(lam > 1.0 / big && lam < big && A.dz > 1.0 / big && A.dz < big);
     if (A.simplex)
-        hipLaunchKernelGGL(k_deposit<true>, grid, dim3(kDepositThreads), lds, st, A, out);
+        hipLaunchKernelGGL(k_deposit<true>, grid, dim3(kDepositThreads), lds, st, B, run, out);
     else
-        hipLaunchKernelGGL(k_deposit<false>, grid, dim3(kDepositThreads), lds, st, A, out);
+        hipLaunchKernelGGL(k_deposit<false>, grid, dim3(kDepositThreads), lds, st, B, run, out);
     return hipGetLastError();
 }
 

@@ -258,6 +258,7 @@ struct DepositArgs {
     int simplex;
     const int32_t *perm_b, *perm_t;
     double lam_b[3], lam_t[3];
+    int exact_div;   // set by launch_deposit: lengths outside the range of the short division
 };
 constexpr int kDepositMaxBeds = 129;   // contacts of a column held in LDS (128 x 64 lanes x 8 B)
 hipError_t launch_deposit(const DepositArgs &A, float *out, hipStream_t st);

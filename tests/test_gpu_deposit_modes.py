@@ -85,3 +85,38 @@ def test_deposit_sinusoidal_matches_the_oracle(case):
     print("%s: deposit_sinusoidal rel-L2 %.2e, max |diff| %.2e m/s" % (case, e, np.abs(got - ref).max()),
           flush=True)
     assert e <= TOL
+
+
+@pytest.mark.parametrize("form", ["simplex", "value"])
+@pytest.mark.parametrize("t,ny,nx,nb,a_B,lam_tz", [(1, 1, 1, 1, 0.0, 35.0), (3, 1, 63, 2, 1.0, 35.0),
+                                                   (5, 8, 8, 129, 2.0, 35.0), (17, 5, 13, 20, 30.0, 1e70),
+                                                   (63, 2, 33, 7, 0.5, 35.0), (130, 1, 70, 60, 8.0, 35.0)])
+def test_deposit_at_the_edges_of_columns_and_depth_runs(form, t, ny, nx, nb, a_B, lam_tz):
+    """Areas of one column to one past a workgroup's 64, bands of one depth,
+    fewer depths than waves and cut into runs, one bed to the most allowed,
+    contacts that cross many others, a wavelength outside the short division's
+    range.  The bar of the other Deposit tests."""
+    rng = np.random.default_rng(t * 100 + nb)
+    thick = rng.uniform(0.3, 2.0, nb).astype(np.float32) * np.float32(t / nb)
+    vbed = rng.normal(2600.0, 150.0, nb).astype(np.float32)
+    off = rng.uniform(0, 300, nb).astype(np.float32)
+    args = (t, ny, nx, 5.0, 10.0, 12.5)
+    f64 = lambda a: a.astype(np.float64)  # noqa: E731
+    if form == "simplex":
+        pb, pt = rng.permutation(256), rng.permutation(256)
+        lam_b, lam_t = (80.0, 300.0, 240.0), (lam_tz, 200.0, 260.0)
+        got = _host(sgwave.deposit_simplex(*args, _dev(thick), _dev(vbed), 0.4, _dev(pb, np.int32), lam_b, a_B,
+                                           _dev(pt, np.int32), lam_t, _dev(off), 50.0, 0.15, 0.2))
+        ref = OB.deposit_simplex(*args, f64(thick), f64(vbed), 0.4, pb, lam_b, a_B, pt, lam_t, f64(off), 50.0, 0.15,
+                                 0.2)
+    else:
+        eta = rng.uniform(-1, 1, (max(nb - 1, 1), ny, nx)).astype(np.float32)
+        tex = rng.uniform(-1, 1, (5, 4, 6)).astype(np.float32)
+        lam = (min(lam_tz, 1e6), 200.0, 260.0)
+        got = _host(sgwave.deposit(*args, _dev(thick), _dev(vbed), 0.4, _dev(eta) if nb > 1 else None, a_B, _dev(tex),
+                                   lam, _dev(off), 50.0, 0.15, 0.2))
+        ref = OB.deposit(*args, f64(thick), f64(vbed), 0.4, f64(eta[:nb - 1]), a_B, f64(tex), lam, f64(off), 50.0,
+                         0.15, 0.2)
+    e = rel_l2(got, ref)
+    print("%s %s: rel-L2 %.2e" % (form, (t, ny, nx, nb), e), flush=True)
+    assert e <= TOL
