@@ -202,3 +202,26 @@ def test_salt_without_a_mask_output_through_the_c_abi():
     assert st == sgwave.SG_OK
     assert torch.equal(out, ref)
     assert (ref == 4500.0).any()
+
+
+@pytest.mark.parametrize("shape,h,frac,amp", [
+    ((17, 13, 63), (10.0, 10.0, 10.0), (0.5, 0.5, 0.5), 0.3), ((16, 12, 64), (8.0, 11.0, 9.0), (0.1, 0.9, 0.05), -0.4),
+    ((9, 31, 65), (10.0, 10.0, 10.0), (0.9, 0.2, 0.97), 0.5), ((33, 6, 128), (5.0, 20.0, 10.0), (0.4, 0.5, 0.5), 0.25),
+    ((24, 9, 129), (10.0, 10.0, 10.0), (0.6, 0.1, 0.3), 0.0), ((41, 27, 192), (10.0, 7.0, 10.0), (0.5, 0.4, 0.33), 0.6)])
+def test_box_word_and_block_edges_match_the_oracle(shape, h, frac, amp):
+    """Rows one voxel short of, equal to and past whole 64-voxel words, planes
+    and rows that do not fill the blocks of the z and y passes, bodies cut off
+    by each side of the volume, a needle and a disc (the z span of a row far
+    from the box's), a field that adds and takes away at distances beyond the
+    body's own size, none at all: mask and volume equal the oracle's."""
+    ext = np.array(shape) * np.array(h)
+    centres = [ext * frac, ext * (0.5, 0.5, 0.6)]
+    radii = [ext * (0.35, 0.3, 0.25), (0.05 * ext.max(), 0.6 * ext.max(), 0.05 * ext.max())]
+    rots = [_rot(0.7, -0.4, 0.9), _rot(0.5, 0.8, -0.6)]
+    grf = (2.0 * _field(2, shape, 1.7, shape[2])).astype(np.float32)
+    V = _model(shape, shape[0])
+    got, mask, ref, K = _run(V, h, centres, radii, rots, grf, amp, 4500.0, 0.0, 3)
+    _report("edges %s" % (shape,), mask, K)
+    assert 0 < K.sum() < K.size
+    assert np.array_equal(mask, K)
+    assert np.array_equal(got, ref.astype(np.float32))
