@@ -128,8 +128,8 @@ typedef struct {
  *                stencil read from global memory; 2 = LDS-tiled, time-blocked
  *                launches; 3 = column sweep: a workgroup walks a strip of
  *                tile_x columns (128 or 256, 0 = 256) from top to bottom --
- *                the whole height, or one segment of tile_z output rows
- *                (0 = whole height, else >= 8) -- advancing time_block (1..6,
+ *                the whole height, or one of equal segments of at most tile_z
+ *                output rows (0 = whole height, else >= 8) -- advancing time_block (1..6,
  *                0 = 4) levels in a skewed pipeline, so only the x halo of
  *                4*time_block per side (and 4*time_block + 4 rows above a
  *                segment) is recomputed (forward calls with dz == dx; the
@@ -657,7 +657,7 @@ sg_status sg_salt_sdt(const float *v, int32_t nz, int32_t ny, int32_t nx, double
  *   out    device floats [nz][ny][nx] (for sg_salt_sdt's grf), not aliasing noise
  *   ws     device workspace of sg_grf_workspace_size bytes (two complex grids)
  * Extents 1..1024; lengths finite and >= 0 (0 leaves an axis white); p >= 0.
- * The 3D transforms are hand-written radix-2 FFTs in FP32.  Stream-ordered,
+ * The 3D transforms are hand-written FFTs in FP32 (one pass in FP64).  Stream-ordered,
  * no allocation; SG_EINVAL / SG_ENOSPACE as usual. */
 sg_status sg_grf_workspace_size(int32_t nz, int32_t ny, int32_t nx, int32_t *grid, size_t *bytes);
 sg_status sg_grf(const float *noise, int32_t nz, int32_t ny, int32_t nx, double lz, double ly, double lx, double p,

@@ -23,6 +23,13 @@
 // the ghost rows -1..-4 of every level hold minus rows 1..4 (odd mirror):
 // when a level produces row R in 1..4 it writes -p into the register slot of
 // row -R, before any row that reads it is computed.
+//
+// Bound: vector issue (71 % of the cycles a CU has work, 256-column strips,
+// time block 5; 26 to 28 vector instructions per lane and update in the plain
+// steps, 20 of them the Laplacian), then the share of a strip's lanes that is
+// halo.  8 uneven slices x 32 shots x 400 updates: 114.1 ms with one form for
+// all steps (best at time block 4, 320-row segments), 87.5 ms with runs of plain
+// steps (time block 5, equal segments of up to 160 rows).
 #include "sg_internal.h"
 
 #include <type_traits>
@@ -81,7 +88,6 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
     // clamped into the guard columns (zeros): no test on columns outside the grid
     const int Xc = min(max(X, -kGuard), s.Nx + kGuard - 1);
     const uint32_t xo4 = (uint32_t)(Xc + kGuard) * 4u;
-    const uint32_t xs4 = (uint32_t)(X + kGuard) * 4u;     // store column (output lanes only)
     const int pitch = s.pitch, Nz = s.Nz;
     auto rowb = [&](int R) -> uint32_t {                    // clamped into the guard rows (zeros)
         R = min(max(R, -kGuard), Nz + kGuard - 1);
@@ -93,23 +99,41 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
     float *out_cur = out_prev + s.frame;
     const bool free_top = s.free_top != 0;
 
-    // rows holding source nodes of this shot (the nodes themselves and the
-    // wavelet samples are read only at those rows; level n+s takes w(t_{n+s-1}))
-    const int32_t *nz_ = s.src_iz + shot * kNodes;
-    const int32_t *nx_ = s.src_ix + shot * kNodes;
-    const float *nw_ = s.src_w + shot * kNodes;
+    // rows holding source nodes of this shot (srow_lo and srow_hi, one below
+    // the other or the same) and this lane's node weight on each of them; the
+    // wavelet samples are read only there (level n+s takes w(t_{n+s-1}))
     const float *wshot = s.wavelet + (int64_t)shot * s.wavelet_stride + t.n;
     int srow_lo = 1 << 30, srow_hi = -(1 << 30);
+    float sw_lo = 0.f, sw_hi = 0.f;
+    {
+        int iz[kNodes], ixn[kNodes];
+        float wn[kNodes];
 #pragma unroll
-    for (int k = 0; k < kNodes; ++k)
-        if (gld(nw_ + k) != 0.f) {
-            srow_lo = min(srow_lo, gld(nz_ + k));
-            srow_hi = max(srow_hi, gld(nz_ + k));
+        for (int k = 0; k < kNodes; ++k) {
+            iz[k] = gld(s.src_iz + shot * kNodes + k);
+            ixn[k] = gld(s.src_ix + shot * kNodes + k);
+            wn[k] = gld(s.src_w + shot * kNodes + k);
         }
+#pragma unroll
+        for (int k = 0; k < kNodes; ++k)
+            if (wn[k] != 0.f) {
+                srow_lo = min(srow_lo, iz[k]);
+                srow_hi = max(srow_hi, iz[k]);
+            }
+        // (the four nodes of a point are four cells: at most one per row and lane)
+#pragma unroll
+        for (int k = 0; k < kNodes; ++k)
+            if (wn[k] != 0.f && ixn[k] == X) {
+                if (iz[k] == srow_lo) sw_lo = wn[k];
+                if (iz[k] == srow_hi) sw_hi = wn[k];
+            }
+        srow_lo = __builtin_amdgcn_readfirstlane(srow_lo);
+        srow_hi = __builtin_amdgcn_readfirstlane(srow_hi);
+    }
     // receivers of this strip (entries sorted by base row); levels n..n+TB-1 due
     int rbeg = 0, rend = 0, rrow_lo = 1 << 30, rrow_hi = -(1 << 30);
     unsigned due = 0;
-    if (s.gathers) {
+    if (!RECOMP && s.gathers) {   // (a recompute records nothing)
         rbeg = gld(s.tile_rec + tile);
         rend = gld(s.tile_rec + tile + 1);
         if (rend > rbeg) {
@@ -121,8 +145,9 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
             if ((t.n + q) % s.rec_every == 0 && q < t.nsteps) due |= 1u << q;
     }
     // steps at which some due level records a receiver row (one range test per step)
-    const int rec_j0 = due && rend > rbeg ? rrow_lo + 6 : 1 << 30;
-    const int rec_j1 = due && rend > rbeg ? rrow_hi + 4 * (TB - 1) + 6 : -(1 << 30);
+    const int rec_j0 = __builtin_amdgcn_readfirstlane(due && rend > rbeg ? rrow_lo + 6 : 1 << 30);
+    const int rec_j1 =
+        __builtin_amdgcn_readfirstlane(due && rend > rbeg ? rrow_hi + 4 * (TB - 1) + 6 : -(1 << 30));
 
     float Q[TB][kQ];
 #pragma unroll
@@ -135,21 +160,24 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
     // zero the rings (pad columns included: read only by discarded halo cells)
     for (int q = threadIdx.x; q < TB * RING; q += NTHR) lds[q] = 0.f;
 
-    // Loads run two steps ahead of their use: step j takes level n at row j,
-    // level n-1 at row j-4 and W, 2a at the rows j-4q its levels compute from
-    // prefetch slot j mod 3 (3 divides the unroll of 9, so slots are
-    // compile-time too) and issues the loads of step j+2 into slot (j+2) mod 3.
-    constexpr int kPf = 3;
-    float pc[kPf], pp[kPf], pw[kPf][TB], pa[kPf][TB];
+    // Loads of the two input levels run two steps ahead of their use: step j
+    // takes level n at row j and level n-1 at row j-4 from prefetch slot j mod 3
+    // (3 divides the unroll of 9, so slots are compile-time too) and issues the
+    // loads of step j+2 into slot (j+2) mod 3.  W and 2a of the rows j-4q go the
+    // same way at time blocks up to 3; beyond, where 16 more registers would
+    // spill, they are loaded one step ahead, level n+q's for step j+1 into the
+    // register its step j has just used (mostly from L2: every level reads each
+    // row in turn).  Time block 3 with one step ahead: 5 % slower.
+    constexpr int kPf = 3, kPw = TB <= 3 ? 3 : 1, kAhead = TB <= 3 ? 2 : 1;
+    float pc[kPf], pp[kPf], pw[kPw][TB], pa[kPw][TB];
     auto issue = [&](const int slotp, const int jj) {
         pc[slotp] = gld_at(in_cur, rowb(jj) + xo4);
         pp[slotp] = gld_at(in_prev, rowb(jj - 4) + xo4);
-#pragma unroll
-        for (int q = 0; q < TB; ++q) {
-            const uint32_t o = rowb(jj - 4 * (q + 1)) + xo4;
-            pw[slotp][q] = gld_at(s.W, o);
-            pa[slotp][q] = gld_at(s.A2, o);
-        }
+    };
+    auto issue_coef = [&](const int slotw, const int q, const int jj) {   // q = 1 .. TB
+        const uint32_t o = rowb(jj - 4 * q) + xo4;
+        pw[slotw][q - 1] = gld_at(s.W, o);
+        pa[slotw][q - 1] = gld_at(s.A2, o);
     };
     // first step: the top segment starts at row -9 (every row above 0 is a
     // guard or ghost row); a lower one TB levels of 4 rows, plus the 4 rows
@@ -158,14 +186,79 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
     // and no output row reads them
     const int jf = zs0 - 4 * TB - kHalo;
     const int j0 = zs0 == 0 ? -kQ : jf - (jf % kQ + kQ) % kQ;
+    pc[2] = pp[2] = 0.f;   // (filled at the first step)
 #pragma unroll
-    for (int q = 0; q < kPf; ++q) {   // (registers of every slot defined; slot 2 is refilled at the first step)
-        pc[q] = pp[q] = 0.f;
+    for (int q = 1; q <= TB; ++q) {
 #pragma unroll
-        for (int r = 0; r < TB; ++r) pw[q][r] = pa[q][r] = 0.f;
+        for (int u = 0; u < kPw; ++u) {
+            if (u < kAhead)
+                issue_coef(u, q, j0 + u);
+            else
+                pw[u][q - 1] = pa[u][q - 1] = 0.f;   // (filled at the first step)
+        }
     }
     issue(0, j0);
     issue(1, j0 + 1);
+
+    // The plain steps: rows past the free top's ghost rows, no source row and no
+    // receiver sample among them.  Nearly all steps of a segment are plain, and
+    // what the others test for (mirror, sources, receivers, rows above the grid,
+    // with the scalar registers that spills) is a third of their instructions, so a group
+    // of kQ plain steps runs in a form without it, and on strips and rows where
+    // every cell has a = 1 (UNIT) without loading 2a.
+    // byte offset of a row past the ghost rows; below the grid that of the last guard row
+    auto rowp = [&](int R) -> uint32_t { return (uint32_t)((min(R, Nz + kGuard - 1) + kGuard) * pitch) * 4u + xo4; };
+    auto plain_step = [&](auto ph, auto unit, const int j) {
+        constexpr int PH = decltype(ph)::value;
+        constexpr bool UNIT = decltype(unit)::value;
+        constexpr int PS = PH % kPf;
+        pc[(PH + 2) % kPf] = gld_at(in_cur, rowp(j + 2));
+        pp[(PH + 2) % kPf] = gld_at(in_prev, rowp(j - 2));
+        if (PH % 3 == 0) __syncthreads();
+        const float cin = pc[PS];
+        Q[0][slot(PH)] = cin;
+        my[slot(PH) * LW] = cin;
+        float vlast = 0.f;
+#pragma unroll
+        for (int q = 1; q <= TB; ++q) {
+            const float(&P)[kQ] = Q[q - 1];
+            const float c = P[slot(PH - 4 * q)];
+            int xa = lane_b + ((q - 1) * RING + slot(PH - 4 * q) * LW - kHalo) * 4;   // column x - 4
+            asm volatile("" : "+v"(xa));
+            const float *xr = (const float *)((const char *)lds + xa);
+            const float c4 = -4.f * c;
+            float lap = 0.f;
+#pragma unroll
+            for (int m = 1; m <= kHalo; ++m) {
+                const float zs = P[slot(PH - 4 * q + m)] + P[slot(PH - 4 * q - m)];
+                lap = fmaf(s.cz[m], (zs + (xr[kHalo + m] + xr[kHalo - m])) + c4, lap);
+            }
+            const float old = q == 1 ? pp[PS] : Q[q - 2][slot(PH - 4 * q)];
+            const float v = fmaf(pw[PH % kPw][q - 1], lap, fmaf(UNIT ? 2.f : pa[PH % kPw][q - 1], c - old, old));
+            {
+                const uint32_t o = rowp(j + kAhead - 4 * q);
+                pw[(PH + kAhead) % kPw][q - 1] = gld_at(s.W, o);
+                if (!UNIT) pa[(PH + kAhead) % kPw][q - 1] = gld_at(s.A2, o);
+            }
+            if (RECOMP && xout && j - 4 * q >= zs0 && j - 4 * q < zs1) {
+                float *rl = t.ring + (int64_t)shot * t.ring_shot + (int64_t)(t.n + q - 1 - t.ring_lo) * s.frame;
+                __builtin_nontemporal_store((v - c) - (c - old),
+                                            (__attribute__((address_space(1))) float *)((char *)rl +
+                                                (uint32_t)((j - 4 * q + kGuard) * pitch) * 4u + xo4));
+            }
+            if (q < TB) {
+                Q[q][slot(PH - 4 * q)] = v;
+                my[q * RING + slot(PH - 4 * q) * LW] = v;
+            } else {
+                vlast = v;
+            }
+        }
+        if (xout && j - 4 * TB >= zs0 && j - 4 * TB < zs1) {
+            const uint32_t o = (uint32_t)((j - 4 * TB + kGuard) * pitch) * 4u + xo4;
+            gst_at(out_cur, o, vlast);
+            gst_at(out_prev, o, Q[TB - 1][slot(PH - 4 * TB)]);
+        }
+    };
 
     auto step = [&](auto ph, const int j) {
         constexpr int PH = decltype(ph)::value;
@@ -182,23 +275,25 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
         Q[0][slot(PH)] = cin;
         my[slot(PH) * LW] = cin;
         if (free_top && j >= 1 && j <= kHalo) Q[0][slot(-PH)] = -cin;
-        // receivers of levels n..n+TB-1 at base row j - 4q - 6
-        if (j >= rec_j0 && j <= rec_j1) {
-#pragma unroll
+        // receivers of levels n..n+TB-1 at base row j - 4q - 6 (a loop, not
+        // unrolled: it touches no register queue, and copies of it in every
+        // phase and level took registers from the plain steps)
+        if (!RECOMP && j >= rec_j0 && j <= rec_j1) {
+#pragma unroll 1
             for (int q = 0; q < TB; ++q) {
                 const int Rb = j - 4 * q - 6;
-                if (((due >> q) & 1u) && Rb >= rrow_lo && Rb <= rrow_hi) {
-                    const float *L0 = lds + q * RING + slot(PH - 4 * q - 6) * LW;
-                    const float *L1 = lds + q * RING + slot(PH - 4 * q - 5) * LW;
-                    float *row = s.gathers + ((int64_t)shot * s.nrow + (t.n + q) / s.rec_every) * s.nrec;
-                    for (int e = rbeg + (int)threadIdx.x; e < rend; e += NTHR) {
-                        const int code = gld(&s.rec_list[e].lds);
-                        if (code / LW != Rb) continue;
-                        const int c = code - Rb * LW;
-                        const float w0 = gld(&s.rec_list[e].w[0]), w1 = gld(&s.rec_list[e].w[1]);
-                        const float w2 = gld(&s.rec_list[e].w[2]), w3 = gld(&s.rec_list[e].w[3]);
-                        row[gld(&s.rec_list[e].r)] = w0 * L0[c] + w1 * L0[c + 1] + w2 * L1[c] + w3 * L1[c + 1];
-                    }
+                if (!((due >> q) & 1u) || Rb < rrow_lo || Rb > rrow_hi) continue;
+                const int s0 = (PH + 8 * kQ - 4 * q - 6) % kQ, s1 = s0 + 1 == kQ ? 0 : s0 + 1;
+                const float *L0 = lds + q * RING + s0 * LW;
+                const float *L1 = lds + q * RING + s1 * LW;
+                float *row = s.gathers + ((int64_t)shot * s.nrow + (t.n + q) / s.rec_every) * s.nrec;
+                for (int e = rbeg + (int)threadIdx.x; e < rend; e += NTHR) {
+                    const int code = gld(&s.rec_list[e].lds);
+                    if (code / LW != Rb) continue;
+                    const int c = code - Rb * LW;
+                    const float w0 = gld(&s.rec_list[e].w[0]), w1 = gld(&s.rec_list[e].w[1]);
+                    const float w2 = gld(&s.rec_list[e].w[2]), w3 = gld(&s.rec_list[e].w[3]);
+                    row[gld(&s.rec_list[e].r)] = w0 * L0[c] + w1 * L0[c + 1] + w2 * L1[c] + w3 * L1[c + 1];
                 }
             }
         }
@@ -223,21 +318,18 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
                 lap = fmaf(s.cz[m], (zs + (xr[kHalo + m] + xr[kHalo - m])) + c4, lap);
             }
             const float old = q == 1 ? pp[PS] : Q[q - 2][slot(PH - 4 * q)];
-            const float Wq = pw[PS][q - 1];
-            float v = fmaf(Wq, lap, fmaf(pa[PS][q - 1], c - old, old));
-            if (R >= srow_lo && R <= srow_hi) {
-                const float wq = gld(wshot + (q - 1));
-#pragma unroll
-                for (int k = 0; k < kNodes; ++k) {
-                    const float wk = gld(nw_ + k);
-                    if (gld(nz_ + k) == R && X == gld(nx_ + k) && wk != 0.f) v = fmaf(Wq, wk * wq, v);
-                }
+            const float Wq = pw[PH % kPw][q - 1];
+            float v = fmaf(Wq, lap, fmaf(pa[PH % kPw][q - 1], c - old, old));
+            issue_coef((PH + kAhead) % kPw, q, j + kAhead);
+            if (R == srow_lo || R == srow_hi) {
+                const float wk = R == srow_lo ? sw_lo : sw_hi;
+                if (wk != 0.f) v = fmaf(Wq, wk * gld(wshot + (q - 1)), v);
             }
             if (RECOMP && R >= zs0 && R < zs1 && xout) {
                 float *rl = t.ring + (int64_t)shot * t.ring_shot + (int64_t)(t.n + q - 1 - t.ring_lo) * s.frame;
                 __builtin_nontemporal_store((v - c) - (c - old),
                                             (__attribute__((address_space(1))) float *)((char *)rl +
-                                                (uint32_t)((R + kGuard) * pitch) * 4u + xs4));
+                                                (uint32_t)((R + kGuard) * pitch) * 4u + xo4));
             }
             if (q < TB) {
                 Q[q][slot(PH - 4 * q)] = v;
@@ -250,7 +342,7 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
         // output: levels n+TB and n+TB-1 at row j - 4TB
         const int R = j - 4 * TB;
         if (R >= zs0 && R < zs1 && xout) {
-            const uint32_t o = (uint32_t)((R + kGuard) * pitch) * 4u + xs4;
+            const uint32_t o = (uint32_t)((R + kGuard) * pitch) * 4u + xo4;
             gst_at(out_cur, o, vlast);
             gst_at(out_prev, o, Q[TB - 1][slot(PH - 4 * TB)]);
         }
@@ -263,7 +355,27 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
     // zeroed before the first step's barrier
     const int nsteps = max(zs1 + 4 * TB, rec_j1 + 1) - j0;
     const int j1 = j0 + (nsteps + kQ - 1) / kQ * kQ;
-    for (int j = j0; j < j1; j += kQ) {
+    // Three runs of groups, one after the other (each keeps its registers from
+    // group to group; with a choice per group they were spilled): the steps up
+    // to the last source row or receiver sample, or to the first row clear of
+    // the ghost rows; the plain ones whose rows j - 4 TB .. j + 4 and columns
+    // all have a = 1; the other plain ones, down to the guard rows.
+    const int jp0 = max(4 * TB + kHalo + 1, max(srow_hi + 4 * TB, rec_j1) + 1);
+    const bool unit_x = ex0 >= s.unit_x0 && ex0 + EX <= s.unit_x1;
+    const int ju0 = max(jp0, s.unit_z0 + 4 * TB), ju1 = min(s.unit_z1 - (kQ - 1) + kHalo, Nz + kGuard - kQ - 1);
+    auto group = [&](auto unit, const int j) {
+        plain_step(std::integral_constant<int, 0>{}, unit, j);
+        plain_step(std::integral_constant<int, 1>{}, unit, j + 1);
+        plain_step(std::integral_constant<int, 2>{}, unit, j + 2);
+        plain_step(std::integral_constant<int, 3>{}, unit, j + 3);
+        plain_step(std::integral_constant<int, 4>{}, unit, j + 4);
+        plain_step(std::integral_constant<int, 5>{}, unit, j + 5);
+        plain_step(std::integral_constant<int, 6>{}, unit, j + 6);
+        plain_step(std::integral_constant<int, 7>{}, unit, j + 7);
+        plain_step(std::integral_constant<int, 8>{}, unit, j + 8);
+    };
+    int j = j0;
+    for (; j < j1 && (j < jp0 || (unit_x && j < ju0)); j += kQ) {
         step(std::integral_constant<int, 0>{}, j);
         step(std::integral_constant<int, 1>{}, j + 1);
         step(std::integral_constant<int, 2>{}, j + 2);
@@ -274,17 +386,27 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
         step(std::integral_constant<int, 7>{}, j + 7);
         step(std::integral_constant<int, 8>{}, j + 8);
     }
+    if (unit_x && j < j1 && j < ju1) {
+        for (; j < j1 && j < ju1; j += kQ) group(std::true_type{}, j);
+        // 2a of the next kAhead steps, which these groups left out
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+            for (int q = 0; q < TB; ++q) pa[u][q] = gld_at(s.A2, rowb(j + u - 4 * (q + 1)) + xo4);
+    }
+    for (; j < j1; j += kQ) group(std::false_type{}, j);
 }
 
+#define SG_SWEEP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(TB <= 4 ? 4 : (TB == 5 ? 3 : 2))))
 template <int NW, int TB, bool RECOMP>
-__global__ void __launch_bounds__(64 * NW) k_sweep(SliceDesc s, TileArgs t)
+__global__ void __launch_bounds__(64 * NW) SG_SWEEP_OCCUPANCY k_sweep(SliceDesc s, TileArgs t)
 {
     __shared__ float lds[TB * kQ * (64 * NW + 2 * kHalo)];
     sweep_body<NW, TB, RECOMP>(s, t, xcd_block(blockIdx.x, gridDim.x), lds);
 }
 
 template <int NW, int TB, bool RECOMP>
-__global__ void __launch_bounds__(64 * NW) k_sweep_batch(const BatchItem *__restrict__ items, int nitems, int n,
+__global__ void __launch_bounds__(64 * NW) SG_SWEEP_OCCUPANCY k_sweep_batch(const BatchItem *__restrict__ items, int nitems, int n,
                                                           LevelPair lv, int ring_lo)
 {
     __shared__ float lds[TB * kQ * (64 * NW + 2 * kHalo)];
@@ -344,7 +466,10 @@ Tiling make_sweep_tiling(int Nz, int Nx, int nw, int tb, int seg_h)
     T.k = 0;
     T.tb = tb;
     T.tx = T.ex - 2 * kHalo * tb;
-    T.tz = seg_h > 0 && seg_h < Nz ? seg_h : Nz;
+    // equal segments of at most seg_h rows (a short last one leaves its
+    // workgroups idle while the others run)
+    const int nseg = seg_h > 0 && seg_h < Nz ? (Nz + seg_h - 1) / seg_h : 1;
+    T.tz = (Nz + nseg - 1) / nseg;
     T.tz_top = T.tz;          // segments are equal from the top (free top or not)
     T.sweep_nw = nw;
     T.ok = (nw == 2 || nw == 4) && tb >= 1 && tb <= kSweepMaxTimeBlock && T.tx >= 1 && seg_h >= 0;

@@ -217,3 +217,48 @@ def test_gradient_with_sweep_forward_and_recompute(tuning, layout, top):
         items_out.append(items[0][4].cpu().numpy())
     assert np.array_equal(items_out[0], items_out[1])
     assert rel_l2(items_out[0], ref) <= TOL
+
+
+WIDE = [dict(variant=3, tile_x=x, tile_z=z, time_block=tb)
+        for x, z, tb in ((128, 0, 1), (256, 0, 2), (128, 70, 3), (256, 64, 4), (256, 0, 5), (128, 90, 5), (256, 100, 6))]
+
+
+@pytest.mark.parametrize("tuning", WIDE, ids=["s%dz%db%d" % (t["tile_x"], t["tile_z"], t["time_block"]) for t in WIDE])
+@pytest.mark.parametrize("top,nbl", [(sgwave.SG_TOP_FREE, 20), (sgwave.SG_TOP_ABSORBING, 9), (sgwave.SG_TOP_FREE, 0)],
+                         ids=["free", "absorbing", "no-sponge"])
+def test_runs_of_plain_steps_equal_the_tiled_kernel(tuning, top, nbl):
+    """A grid tall and wide enough for every kind of step: strips and rows with
+    a = 1 throughout and not, groups before, between and after source rows and
+    receivers (a shallow and a deep source, receivers along the surface and one
+    far below in a single strip), the last rows above the guard rows, segments
+    that hold none of them.  Gathers and snapshots equal the tiled kernel's bit
+    for bit."""
+    nz, nx, h, nt = 181, 700, 10.0, 97
+    g = Geometry(nz=nz, nx=nx, dz=h, dx=h, dt=8e-4, nt=nt, nbl=nbl, vmax_hint=4500.0, top=top, snap_every=24,
+                 snap_count=5)
+    v = synth.field_slice(12, nz, nx)
+    src = np.array([[10.0, 3456.0], [1203.0, 5002.5]])
+    rec = np.concatenate([synth.surface_receivers(nx, h), np.array([[1500.0, 1033.0], [1797.5, 6990.0]])])
+    wl = np.stack([oracle.ricker(25.0, g.dt, nt, t0=0.02)] * 2)
+    a, b = run(g, v, src, rec, wl, tuning), run(g, v, src, rec, wl, TILED)
+    assert np.abs(b[0]).max() > 0 and np.abs(b[1][1, -1]).max() > 0
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("tuning", WIDE, ids=["s%dz%db%d" % (t["tile_x"], t["tile_z"], t["time_block"]) for t in WIDE])
+def test_recompute_on_runs_of_plain_steps_equals_the_tiled_gradient(tuning):
+    """The same grid's gradient: the sweep's forward and recompute give the
+    same second differences as the tiled kernel's, so with the same adjoint the
+    gradient is the same bit for bit."""
+    from test_gpu_gradient import gpu_gradient
+    nz, nx, h, nt = 181, 700, 10.0, 60
+    g = Geometry(nz=nz, nx=nx, dz=h, dx=h, dt=8e-4, nt=nt, nbl=20, vmax_hint=4500.0)
+    v = synth.field_slice(13, nz, nx)
+    src = np.array([[10.0, 3456.0], [1203.0, 5002.5]])
+    rec = synth.surface_receivers(nx, h)
+    wl = oracle.ricker(25.0, g.dt, nt, t0=0.02)
+    resid = np.random.default_rng(3).standard_normal((2, g.nrow, nx)).astype(np.float32)
+    a = gpu_gradient(g, v, src, rec, wl, resid, ckpt=17, tuning=tuning)
+    b = gpu_gradient(g, v, src, rec, wl, resid, ckpt=17)
+    assert np.abs(b[0]).max() > 0
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
