@@ -144,7 +144,10 @@ typedef struct {
  *   rows_per_thread   rows of the tile column each thread keeps in registers
  *                (variant 2): 8 or 16 for 128x64, 16 for 64x128, 8 for 64x64;
  *                0 = the first built one
- * All zeros ask for the library's default.  sg_plan_set_tuning rejects
+ * All zeros ask for the library's default: 128x64 and the time blocks above
+ * (what sg_plan_get_tuning reports), but a single call small enough to run in
+ * finer tiles or longer time blocks with every tile resident at once does so,
+ * with the same gathers and snapshots.  sg_plan_set_tuning rejects
  * shapes that are not built with SG_EUNSUPPORTED.
  */
 typedef struct {

@@ -132,6 +132,7 @@ struct TileArgs {
     int64_t ring_shot;  // floats per shot in the ring
     // adjoint only
     const float *resid; // [nshot][nrow][nrec], dJ/dd at the recorded levels
+    int32_t sum_levels; // levels of one FP32 partial sum of h
     double *hsum;       // [frame] sum over shots and n of mu^{n+1} (p^{n+1} - 2p^n + p^{n-1}), accumulated in FP64
     int32_t nt;
     InjTables inj;
@@ -182,6 +183,10 @@ constexpr int kSweepMaxTimeBlock = 6;
 struct TiledShape { int ex, ez, k; };
 constexpr int kTiledShapes = 4;
 TiledShape tiled_shape(int config);
+// One more, which no tuning names: 64 x 64 cells, 4 rows per thread (1024
+// threads).  The library's default takes it for small launches (single calls).
+constexpr int kFineShape = kTiledShapes;
+int device_cus();
 
 // Kernel launchers (sg_kernels.hip).  All return hipSuccess or the launch error.
 // launch_prepare fills V2, W and A2 (needs gx and gz in place).

@@ -265,11 +265,12 @@ struct TileShape {
 //             nodes of the new level; alongside h += mu^{k+1} D^k for k <= nt-2,
 //             D^k read from the ring (the velocity gradient is 2 / (dt^2 v^3) h:
 //             the damping terms of the exact derivative cancel because eta does
-//             not depend on v).  The launch's FP32 partial sum of h over its
-//             levels is stored in the ring slot of its first level t.n (D^{t.n}
-//             is dead once read; each output cell's slot is read and written by
-//             its own thread only), and k_fold_partials adds the partials of a
-//             segment to the FP64 accumulator in launch order.
+//             not depend on v).  The FP32 partial sum of h over each
+//             t.sum_levels levels of the launch (one such group, or two) is
+//             stored in the ring slot of the group's first level k (D^k is dead
+//             once read; each output cell's slot is read and written by its own
+//             thread only), and k_fold_partials adds the partials of a segment
+//             to the FP64 accumulator in launch order.
 enum { kFwd = 0, kRing = 1, kAdj = 2 };
 
 template <int K, int NWX, int NWZ, int MODE, bool ISO, bool STREAM = false>
@@ -509,6 +510,15 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
 #pragma unroll
         for (int k = 0; k < K; ++k) hp[k] = 0.f;
     }
+    // stores the partial sums of the group whose first level is n and clears them
+    auto store_sums = [&](const int n) {
+        float *hpart = t.ring + (int64_t)shot * t.ring_shot + (int64_t)(n - t.ring_lo) * s.frame;
+#pragma unroll
+        for (int k = 0; k < (ADJ ? K : 1); ++k) {
+            if (xout && k >= k_lo && k < k_hi) gstore_nt_at(hpart, rowb(k) + xo4, hp[k]);
+            hp[k] = 0.f;
+        }
+    };
     __syncthreads();
 
     // One sub-step.  PAR selects the roles: cur (level n forward, mu^{n+1}
@@ -534,6 +544,11 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
             for (int q = rbeg + NTHR + (int)threadIdx.x; q < rend; q += NTHR) sample(gload_rec(s.rec_list + q));
         }
         if (ADJ) {
+            // (a second group only in launches that run in one round: built into
+            // all, it cost the 16-shot gradient 4 %)
+            if constexpr (STREAM) {
+                if (st == t.sum_levels) store_sums(t.n);
+            }
             // imaging term n (needs mu^{n+1} = cur): h += mu^{n+1} D^n, then the
             // loads of D^{n-1} for the next sub-step go out, to land while this
             // sub-step computes
@@ -673,9 +688,9 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
     // the newest level is in A after an even number of sub-steps, else in B
     const bool odd = t.nsteps & 1;
 
-    // ---- write the output tile: the last two levels; the adjoint stores this
-    // launch's partial imaging sums in the ring slot of level t.n
-    float *hpart = ADJ ? t.ring + (int64_t)shot * t.ring_shot + (int64_t)(t.n - t.ring_lo) * s.frame : nullptr;
+    // ---- write the output tile: the last two levels, and the adjoint's last
+    // partial imaging sums
+    if (ADJ) store_sums(STREAM && t.nsteps > t.sum_levels ? t.n - t.sum_levels : t.n);
     // STREAM (a launch whose workgroups all run at once): the levels go out
     // with streaming (non-temporal) stores.  The next launch starts with cold
     // caches anyway, and the end of this one then has little dirty data left
@@ -693,7 +708,6 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
                     gstore_at(out_cur, ob, vc);
                     gstore_at(out_prev, ob, vp);
                 }
-                if (ADJ) gstore_nt_at(hpart, ob, hp[k]);
             }
         }
     }
@@ -909,7 +923,7 @@ hipError_t launch_record_slot(const SliceDesc &s, int n, int slot, hipStream_t s
 namespace {
 // (ex, ez, k) of the instantiations below; every one fits its register
 // budget without spilling.
-constexpr TiledShape kShapes[kTiledShapes] = {{128, 64, 8}, {64, 128, 16}, {64, 64, 8}, {128, 64, 16}};
+constexpr TiledShape kShapes[kTiledShapes + 1] = {{128, 64, 8}, {64, 128, 16}, {64, 64, 8}, {128, 64, 16}, {64, 64, 4}};
 }
 
 TiledShape tiled_shape(int config) { return kShapes[config]; }
@@ -976,8 +990,8 @@ hipError_t launch_adjoint_tiled_batch(const BatchItem *items, int nitems, int to
                                                      ring_hi, st);
 }
 
-// Compute units of the current device (cached per device).
-static int device_cus()
+// Compute units of the current device (cached per device; 0 without one).
+int device_cus()
 {
     static std::atomic<int> cache[64];
     int dev = 0;
@@ -998,6 +1012,9 @@ static hipError_t launch_tiled_as(const SliceDesc &s, const TileArgs &t, int con
     case 1: hipLaunchKernelGGL((k_tiled<16, 1, 8, MODE, ISO, STREAM>), dim3(blocks), dim3(512), 0, st, s, t); break;
     case 2: hipLaunchKernelGGL((k_tiled<8, 1, 8, MODE, ISO, STREAM>), dim3(blocks), dim3(512), 0, st, s, t); break;
     case 3: hipLaunchKernelGGL((k_tiled<16, 2, 4, MODE, ISO, STREAM>), dim3(blocks), dim3(512), 0, st, s, t); break;
+    case kFineShape:
+        hipLaunchKernelGGL((k_tiled<4, 1, 16, MODE, ISO, STREAM>), dim3(blocks), dim3(1024), 0, st, s, t);
+        break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1009,7 +1026,7 @@ static hipError_t launch_tiled(const SliceDesc &s, const TileArgs &t, int config
     const unsigned blocks = (unsigned)(t.ntx * t.ntz * s.nshot);
     // all workgroups resident at once (one 1024-thread or two 512-thread
     // workgroups per compute unit): streaming stores for the output levels
-    const bool one_round = blocks <= (unsigned)device_cus() * (config == 0 ? 1u : 2u);
+    const bool one_round = blocks <= (unsigned)device_cus() * (config == 0 || config == kFineShape ? 1u : 2u);
     return one_round ? launch_tiled_as<MODE, ISO, true>(s, t, config, blocks, st)
                      : launch_tiled_as<MODE, ISO, false>(s, t, config, blocks, st);
 }

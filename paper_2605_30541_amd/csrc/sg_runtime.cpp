@@ -315,6 +315,9 @@ int shape_of(const sg_tuning &t)
     return -1;
 }
 
+// The gradient calls' default time block.
+constexpr int kAdjointBlock = 3;
+
 // Tuning of a call: the plan's setting with zeros replaced by defaults (time
 // block 4 for forward calls, 3 for the gradient calls, the fastest in
 // measurements of each on the field-scale workloads).
@@ -338,10 +341,49 @@ sg_tuning resolve_tuning(const sg_plan *p, int nshot, bool gradient = false)
         t.tile_x = 128;
         t.tile_z = 64;
     }
-    if (t.time_block <= 0) t.time_block = gradient ? 3 : 4;
+    if (t.time_block <= 0) t.time_block = gradient ? kAdjointBlock : 4;
     const int c = shape_of(t);
     if (c >= 0) t.rows_per_thread = sg::tiled_shape(c).k;
     return t;
+}
+
+// The default's tiling of a small single call.  A launch costs ~5 us before and
+// after its sub-steps whatever its size, so where the tiles leave compute units
+// idle it pays to cut them smaller and give each workgroup more levels, halo and
+// all: the first entry, fewest us per level first, whose tiles all run at once
+// (one workgroup per CU).  Measured for 500 levels of one shot, against 128 x 64
+// tiles at time block 4: 104 x 168 padded cells 1369 -> 755 us (64 x 64 x 4, time
+// block 7), 280 x 380 1382 -> 922 (5), 380 x 580 1403 -> 1046 (4), 440 x 640
+// 1406 -> 1134 (128 x 64, 6), 520 x 800 1414 -> 1272 (5).  Past one round it
+// loses (600 x 980 at time block 5: 2178 us against 1423).  The adjoint takes
+// multiples of its own time block only: its partial imaging sums then cover the
+// same levels, and the gradient is the same bit for bit.  Gradients of 500 levels
+// against 128 x 64 tiles at time block 3: 104 x 168 cells and two shots 6700 ->
+// 3312, 280 x 380 6790 -> 4231, 440 x 640 6962 -> 4867, 520 x 800 7090 -> 5455,
+// 600 x 980 7287 -> 6644.  False where nothing fits.
+bool one_round_tiling(const sg_plan *p, int nshot, bool adjoint, sg_tuning *t, int *config, sg::Tiling *T)
+{
+    struct Entry { int config, time_block; };
+    constexpr Entry fwd[] = {{sg::kFineShape, 7}, {sg::kFineShape, 6}, {sg::kFineShape, 5}, {sg::kFineShape, 4},
+                             {0, 6}, {0, 5}, {0, 4}};
+    constexpr Entry adj[] = {{sg::kFineShape, 2 * kAdjointBlock}, {0, 2 * kAdjointBlock},
+                             {sg::kFineShape, kAdjointBlock}};
+    const int cus = sg::device_cus();
+    const Entry *o = adjoint ? std::begin(adj) : std::begin(fwd), *end = adjoint ? std::end(adj) : std::end(fwd);
+    for (; o != end; ++o) {
+        const sg::TiledShape sh = sg::tiled_shape(o->config);
+        const sg::Tiling f = sg::make_tiling(p->Nz, p->Nx, p->g.top == SG_TOP_FREE, sh.ex, sh.ez, sh.k, o->time_block);
+        const int64_t tiles = (int64_t)f.ntx * f.ntz;
+        if (!f.ok || tiles > max_tiles(p) || tiles * nshot > cus) continue;
+        t->tile_x = sh.ex;
+        t->tile_z = sh.ez;
+        t->rows_per_thread = sh.k;
+        t->time_block = o->time_block;
+        *config = o->config;
+        *T = f;
+        return true;
+    }
+    return false;
 }
 
 sg_status tiling_for(const sg_plan *p, const sg_tuning &t, int *config, sg::Tiling *T)
@@ -568,6 +610,7 @@ sg::TileArgs tile_args(const sg::Tiling &T, float *fields, int64_t frame, int n,
     a.tz_top = T.tz_top;
     a.ntx = T.ntx;
     a.ntz = T.ntz;
+    a.sum_levels = T.tb;
     a.fields = fields;
     sg::set_levels(a, frame, sg::LevelPair{in_pair});
     return a;
@@ -653,7 +696,7 @@ int level_slot(const sg_tuning &t, int m, int pair) { return t.variant == 1 ? (m
 // Shared validation and set-up of the calls on one slice.  The gradient
 // calls keep two tilings: T for the adjoint (always the tiled kernel) and Tf
 // for the forward and its recompute (the column sweep when the plan's tuning
-// asks for it, else the same as T).
+// asks for it); the other calls use Tf.
 struct CallSetup {
     Layout L;
     sg_tuning t;
@@ -662,6 +705,7 @@ struct CallSetup {
     sg_tuning tf;
     int config_f = -1;
     sg::Tiling Tf{};
+    int sum_levels = 0;        // levels of one partial imaging sum of the adjoint
 };
 
 sg_status setup_call(sg_plan *p, const float *vp, const sg_shots *shots, void *ws, size_t ws_bytes, int ckpt,
@@ -693,6 +737,15 @@ sg_status setup_call(sg_plan *p, const float *vp, const sg_shots *shots, void *w
         c->config_f = c->config;
         c->Tf = c->T;
     }
+    c->sum_levels = c->t.time_block;
+    // what the library chooses by itself: the whole call, or the tiled part of
+    // a gradient beside a sweep or a one-level tuning
+    const sg_tuning &set = p->tuning;
+    const bool all = set.variant == 0 && set.tile_x == 0 && set.tile_z == 0 && set.rows_per_thread == 0 &&
+                     set.time_block == 0;
+    if (all || (gradient && set.variant == 1)) one_round_tiling(p, shots->nshot, false, &c->tf, &c->config_f, &c->Tf);
+    if (gradient && (all || set.variant == 1 || set.variant == 3))
+        one_round_tiling(p, shots->nshot, true, &c->t, &c->config, &c->T);
     return SG_OK;
 }
 
@@ -940,14 +993,14 @@ sg_status forward_call(sg_plan *p, const float *vp, const sg_shots *shots, float
     if (rc != SG_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     char *w = (char *)ws;
-    if ((rc = upload_tables(p, c.L, w, shots, c.t.variant >= 2 ? &c.T : nullptr, st, !no_alloc)) != SG_OK)
+    if ((rc = upload_tables(p, c.L, w, shots, c.tf.variant >= 2 ? &c.Tf : nullptr, st, !no_alloc)) != SG_OK)
         return rc;
     const sg::SliceDesc s = describe(p, c.L, w, shots, gathers, snaps);
     SG_HIP(sg::launch_prepare(s, vp, (float)(p->g.dt * p->g.dt), st));
     SG_HIP(sg::launch_zero(s.fields, (size_t)shots->nshot * sg::kFramesPerShot * p->frame, st));
     // recording and instantiating a graph allocates: without allocation the
     // launches are enqueued directly
-    return run_forward(p, s, c.t, c.config, c.T, st, !no_alloc);
+    return run_forward(p, s, c.tf, c.config_f, c.Tf, st, !no_alloc);
 }
 
 sg_status report_error(sg_status st, const char *msg) { return fail(st, "%s", msg); }
@@ -1408,15 +1461,14 @@ sg_status sg_adjoint_gradient(sg_plan *p, const float *vp, const sg_shots *shots
         }
         // adjoint steps k = hi .. lo (mu^k from mu^{k+1}, mu^{k+2}) with imaging;
         // each launch leaves its partial sums in the ring slot of its first level
-        int nlaunch = 0;
         for (int k0 = hi; k0 >= lo;) {
-            ++nlaunch;
             const int nsteps = std::min(c.t.time_block, k0 - lo + 1);
             sg::TileArgs a = tile_args(c.T, mu, F, k0, nsteps, mpair);
             a.ring = ring;
             a.ring_lo = lo;
             a.ring_hi = last - 1;
             a.ring_shot = ring_shot;
+            a.sum_levels = c.sum_levels;
             a.resid = resid;
             a.hsum = hsum;
             a.nt = nt;
@@ -1429,7 +1481,8 @@ sg_status sg_adjoint_gradient(sg_plan *p, const float *vp, const sg_shots *shots
         // segment recomputes into the other ring
         SG_HIP(hipEventRecord(p->ev_seg, st));
         SG_HIP(hipStreamWaitEvent(p->side, p->ev_seg, 0));
-        SG_HIP(sg::launch_fold_partials(s, hsum, ring, ring_shot, hi - lo, c.t.time_block, nlaunch, p->side));
+        SG_HIP(sg::launch_fold_partials(s, hsum, ring, ring_shot, hi - lo, c.sum_levels,
+                                        (hi - lo + c.sum_levels) / c.sum_levels, p->side));
         SG_HIP(hipEventRecord(p->ev_fold[j & 1], p->side));
         folding[j & 1] = true;
     }

@@ -1,0 +1,89 @@
+"""The tilings the library picks for small single calls (every tile of a launch
+resident at once): each entry of its list is reached by one grid size, ragged
+against the tile, with one shot or several, both tops, equal and unequal grid
+spacings.  Gathers and snapshots equal those of 128 x 64
+tiles at time block 4 bit for bit (the same update expression); gradients
+equal the FP64 oracle's to relative L2 <= 1e-4, the bar of every propagation
+test, and those of 128 x 64 tiles at time block 3 bit for bit.  A tuning the caller sets is never replaced."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2605_30541_amd import sgwave
+from paper_2605_30541_amd.sgwave import Geometry, Plan, Shots
+from test_gpu_gradient import _og, gpu_gradient, rel_l2
+from test_gpu_sweep import run
+
+pytestmark = pytest.mark.gpu
+
+EXPLICIT = dict(variant=2, tile_x=128, tile_z=64, time_block=4)
+
+
+# padded cells nz + 2 nbl (free top: nz + nbl) by nx + 2 nbl, over 256 CUs
+@pytest.mark.parametrize("nz,nx,nbl,nshot", [
+    (5, 3, 0, 1), (8, 9, 0, 2), (64, 128, 20, 1), (65, 129, 20, 2), (81, 107, 9, 3), (131, 257, 17, 1),
+    (200, 300, 40, 1), (301, 501, 40, 1), (361, 563, 40, 1), (441, 719, 40, 1), (521, 901, 40, 1),
+    (300, 500, 40, 3)])
+@pytest.mark.parametrize("top", [sgwave.SG_TOP_FREE, sgwave.SG_TOP_ABSORBING], ids=["free", "absorbing"])
+@pytest.mark.parametrize("dz", [10.0, 8.0], ids=["square", "unequal"])
+def test_small_forward_equals_wide_tiles(nz, nx, nbl, nshot, top, dz):
+    rng = np.random.default_rng(nz + nx)
+    nt = 85                                     # 84 steps: not a multiple of 5 or of 8
+    g = Geometry(nz=nz, nx=nx, dz=dz, dx=10.0, dt=8e-4, nt=nt, nbl=nbl, top=top, vmax_hint=3000.0,
+                 snap_every=23, snap_count=3)
+    v = rng.uniform(1800.0, 3000.0, (nz, nx)).astype(np.float32)
+    at = lambda n: np.stack([rng.uniform(0, (nz - 1) * dz, n), rng.uniform(0, (nx - 1) * 10.0, n)], 1)
+    src, rec = at(nshot), np.concatenate([at(40), [[0.0, 0.0], [(nz - 1) * dz, (nx - 1) * 10.0]]])
+    wl = np.stack([oracle.ricker(35.0 + k, g.dt, nt, t0=0.012) for k in range(nshot)])
+    a = run(g, v, src, rec, wl, {})
+    b = run(g, v, src, rec, wl, EXPLICIT)
+    for k in range(2):
+        assert np.any(b[k] != 0)
+        assert np.array_equal(a[k], b[k])
+
+
+# the list's entries in turn; then a call too large for any of them
+@pytest.mark.parametrize("nz,nx,nbl,nshot,top", [
+    (5, 7, 0, 1, sgwave.SG_TOP_FREE), (40, 51, 11, 3, sgwave.SG_TOP_ABSORBING),
+    (64, 128, 20, 2, sgwave.SG_TOP_FREE), (200, 300, 40, 1, sgwave.SG_TOP_FREE),
+    (301, 501, 40, 1, sgwave.SG_TOP_ABSORBING), (361, 563, 40, 1, sgwave.SG_TOP_FREE),
+    (441, 719, 40, 1, sgwave.SG_TOP_FREE), (521, 901, 40, 1, sgwave.SG_TOP_FREE),
+    (300, 500, 40, 4, sgwave.SG_TOP_FREE)])
+def test_small_gradient_matches_oracle(nz, nx, nbl, nshot, top):
+    rng = np.random.default_rng(nz * 1000 + nx)
+    nt, hi = 60, np.array([(nz - 1) * 10.0, (nx - 1) * 10.0])
+    g = Geometry(nz=nz, nx=nx, dz=10.0, dx=10.0, dt=1e-3, nt=nt, nbl=nbl, top=top, vmax_hint=3000.0)
+    v = rng.uniform(1800.0, 3000.0, (nz, nx)).astype(np.float32)
+    src = rng.uniform(0, 1, (nshot, 2)) * hi
+    near = np.repeat(src, 3, 0) + rng.uniform(-60, 60, (3 * nshot, 2))   # within reach of the 59 levels
+    rec = np.clip(near, 0, hi)
+    wl = oracle.ricker(40.0, g.dt, nt, t0=0.012)
+    resid = rng.standard_normal((nshot, g.nrow, len(rec))).astype(np.float32)
+    ref = oracle.gradient(_og(g), v.astype(np.float64), src, wl, rec, resid.astype(np.float64))
+    d_ref, _ = oracle.forward(_og(g), v.astype(np.float64), src, wl, rec)
+    got, gathers = gpu_gradient(g, v, src, rec, wl, resid, ckpt=13)
+    assert np.linalg.norm(d_ref[:, -1]) > 0 and np.linalg.norm(ref) > 0
+    assert rel_l2(gathers, d_ref) <= 1e-4
+    assert rel_l2(got, ref) <= 1e-4
+    # the partial imaging sums cover the same levels whatever the tiling
+    for tuning in (dict(variant=2, tile_x=128, tile_z=64, time_block=3), dict(variant=3, tile_x=128, time_block=3)):
+        same, _ = gpu_gradient(g, v, src, rec, wl, resid, ckpt=13, tuning=tuning)
+        assert np.array_equal(got, same)
+
+
+def test_set_tunings_stand():
+    """The launches the plan counts are those of the time block it was given."""
+    import torch
+    g = Geometry(nz=64, nx=128, dz=10.0, dx=10.0, dt=1e-3, nt=41, nbl=20, vmax_hint=3000.0)
+    v = torch.full((64, 128), 2000.0, device="cuda")
+    wl = torch.from_numpy(oracle.ricker(30.0, g.dt, g.nt).astype(np.float32)).cuda()
+    got = {}
+    for tb in (0, 1, 2, 4, 5, 6):
+        plan = Plan(g)
+        if tb:
+            plan.set_tuning(variant=2, time_block=tb)
+        plan.set_profiling(True)
+        sgwave.forward(plan, v, Shots([[10.0, 400.0]], [[10.0, 640.0]], wl[None]))
+        torch.cuda.synchronize()
+        got[tb] = plan.profile()[1]
+    assert got == {0: 6, 1: 40, 2: 20, 4: 10, 5: 8, 6: 7}
