@@ -230,6 +230,15 @@ __device__ inline int xcd_remap(int b, int nblocks)
     return (b & 7) * per + (b >> 3);
 }
 
+// A pointer that is the same in every lane, as a scalar.
+template <class T>
+__device__ __forceinline__ T *uniform(T *p)
+{
+    const uint64_t v = (uint64_t)p;
+    return (T *)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+}
+
 template <int K, int NWX, int NWZ>
 struct TileShape {
     static constexpr int EX = 64 * NWX, EZ = K * NWZ, NTHR = 64 * NWX * NWZ;
@@ -317,8 +326,6 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
 
     const float *in_prev = t.in + (int64_t)shot * t.in_shot;
     const float *in_cur = in_prev + s.frame;
-    float *out_prev = t.out + (int64_t)shot * t.out_shot;
-    float *out_cur = out_prev + s.frame;
     // byte offset in a stored field of (row Z0 + k, column X): a uniform row
     // part rowb(k) plus the lane's column part xo4 (xc4 at the clamped column)
     auto rowb = [&](int k) { return (uint32_t)((Z0 + k + kGuard) * s.pitch) * 4u; };
@@ -435,6 +442,25 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
     // weight; the wavelet samples of this launch go to LDS.  The receiver
     // entries of the tile: the first NTHR are copied to LDS.
     __shared__ float wav_s[kMaxTimeBlock];
+    // What only the recording and the final stores need waits in LDS instead of
+    // in scalar registers, which run short here (spilled ones are moved through
+    // vector lanes, inside the sub-steps as well: 57 reads in the batched forward
+    // kernel, now none).  A 660 x 1081 shot of 2001 levels 5644 -> 5546 us; batches
+    // of 64 x 64 tiles 4552 -> 4264 us (40 shots of 4 slices, 211 levels).
+    struct Late {
+        float *out, *gathers, *ring;
+        const RecEntry *rec;
+    };
+    __shared__ Late late_s;
+    if (threadIdx.x == 0) {
+        late_s.out = t.out + (int64_t)shot * t.out_shot;
+        if (MODE == kFwd) {
+            late_s.gathers = s.gathers + (int64_t)shot * s.nrow * s.nrec;
+            late_s.rec = s.rec_list;
+        } else {
+            late_s.ring = t.ring + (int64_t)shot * t.ring_shot;
+        }
+    }
     __shared__ RecEntry rec_s[MODE == kFwd ? NTHR : 1];
     bool has_src = false;
     int sk0 = -1, sk1 = -1;
@@ -498,21 +524,20 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
     // is read once), and the partial sums of h.  Only the output cells are
     // read and their sums stored.
     float pn[ADJ ? K : 1], hp[ADJ ? K : 1];
-    const float *ringb = ADJ ? t.ring + (int64_t)shot * t.ring_shot : nullptr;
-    auto ring_level = [&](int L, float(&dst)[ADJ ? K : 1]) {
+    auto ring_level = [&](const float *ringb, int L, float(&dst)[ADJ ? K : 1]) {
         const bool h = xout && L >= t.ring_lo && L <= t.ring_hi;
         const float *rl = ringb + (int64_t)(h ? L - t.ring_lo : 0) * s.frame;
 #pragma unroll
         for (int k = 0; k < K; ++k) dst[k] = (h && k >= k_lo && k < k_hi) ? gload_nt_at(rl, rowb(k) + xc4) : 0.f;
     };
     if (ADJ) {
-        ring_level(t.n, pn);
+        ring_level(t.ring + (int64_t)shot * t.ring_shot, t.n, pn);
 #pragma unroll
         for (int k = 0; k < K; ++k) hp[k] = 0.f;
     }
     // stores the partial sums of the group whose first level is n and clears them
     auto store_sums = [&](const int n) {
-        float *hpart = t.ring + (int64_t)shot * t.ring_shot + (int64_t)(n - t.ring_lo) * s.frame;
+        float *hpart = uniform(late_s.ring) + (int64_t)(n - t.ring_lo) * s.frame;
 #pragma unroll
         for (int k = 0; k < (ADJ ? K : 1); ++k) {
             if (xout && k >= k_lo && k < k_hi) gstore_nt_at(hpart, rowb(k) + xo4, hp[k]);
@@ -534,14 +559,15 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
 
         if (MODE == kFwd && rend > rbeg && n % s.rec_every == 0) {
             // record level n: receivers whose base node is in this output tile
-            float *row = s.gathers + ((int64_t)shot * s.nrow + n / s.rec_every) * s.nrec;
+            float *row = late_s.gathers + (int64_t)(n / s.rec_every) * s.nrec;
+            const RecEntry *list = late_s.rec;
             const float *Lc = lds + lc;
             auto sample = [&](const RecEntry &e) {
                 gstore(row + e.r, e.w[0] * Lc[e.lds] + e.w[1] * Lc[e.lds + 1] + e.w[2] * Lc[e.lds + LW] +
                                       e.w[3] * Lc[e.lds + LW + 1]);
             };
             if (rbeg + (int)threadIdx.x < rend) sample(rec_s[threadIdx.x]);
-            for (int q = rbeg + NTHR + (int)threadIdx.x; q < rend; q += NTHR) sample(gload_rec(s.rec_list + q));
+            for (int q = rbeg + NTHR + (int)threadIdx.x; q < rend; q += NTHR) sample(gload_rec(list + q));
         }
         if (ADJ) {
             // (a second group only in launches that run in one round: built into
@@ -557,7 +583,7 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
                 for (int k = 0; k < K; ++k)
                     if (k >= k_lo && k < k_hi) hp[k] = fmaf(cur[k], pn[k], hp[k]);
             }
-            if (st + 1 < t.nsteps) ring_level(n - 1, pn);
+            if (st + 1 < t.nsteps) ring_level(uniform(late_s.ring), n - 1, pn);
         }
 
         // rows still needed after this sub-step (local rows [need_lo, need_hi))
@@ -595,8 +621,7 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
             const float wav = SRC ? wav_s[st] : 0.f;
             // kRing: the ring slot of D^n (read back by the adjoint only after
             // the whole segment: streaming stores)
-            float *rl_new = MODE == kRing ? t.ring + (int64_t)shot * t.ring_shot + (int64_t)(n - t.ring_lo) * s.frame
-                                          : nullptr;
+            float *rl_new = MODE == kRing ? uniform(late_s.ring) + (int64_t)(n - t.ring_lo) * s.frame : nullptr;
             float xa[2 * kHalo], xb[2 * kHalo];
             if (kAhead) xrow(xa);
 #pragma unroll
@@ -691,6 +716,7 @@ __device__ __forceinline__ void tiled_body(const SliceDesc &s, const TileArgs &t
     // ---- write the output tile: the last two levels, and the adjoint's last
     // partial imaging sums
     if (ADJ) store_sums(STREAM && t.nsteps > t.sum_levels ? t.n - t.sum_levels : t.n);
+    float *out_prev = uniform(late_s.out), *out_cur = out_prev + s.frame;
     // STREAM (a launch whose workgroups all run at once): the levels go out
     // with streaming (non-temporal) stores.  The next launch starts with cold
     // caches anyway, and the end of this one then has little dirty data left
