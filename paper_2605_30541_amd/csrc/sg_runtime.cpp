@@ -1592,7 +1592,7 @@ sg_status batch_forward_impl(const sg_batch_item *items, int32_t nitems, const s
         for (int n = 0; n < nlast;) {
             const int k = std::min(std::min(tb, nlast - n), next_cut(n) - n);
             if (sweep_nw > 0)
-                SG_HIP(sg::launch_sweep_batch(dev_items, nitems, (int)total_blocks, n, k, {pair}, sweep_nw, s2));
+                SG_HIP(sg::launch_sweep_batch(dev_items, nitems, (int)total_blocks, n, k, {pair}, sweep_nw, true, s2));
             else
                 SG_HIP(sg::launch_step_tiled_batch(dev_items, nitems, (int)total_blocks, n, k, {pair}, config, iso, s2));
             pair ^= 1;
@@ -1907,7 +1907,7 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             if (n % C == 0) lv.in_ck = n / C;
             if ((n + k) % C == 0) lv.out_ck = (n + k) / C;
             if (sweep_fwd)
-                SG_HIP(sg::launch_sweep_batch(dev_fwd, na, start, n, k, lv, Tf[0].sweep_nw, st));
+                SG_HIP(sg::launch_sweep_batch(dev_fwd, na, start, n, k, lv, Tf[0].sweep_nw, false, st));
             else
                 SG_HIP(sg::launch_step_tiled_batch(dev_fwd, na, start, n, k, lv, config, iso, st));
             pair ^= 1;
@@ -1931,7 +1931,7 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
                 sg::LevelPair lv{fp};
                 if (n == lo) lv.in_ck = j;
                 if (sweep_fwd)
-                    SG_HIP(sg::launch_sweep_batch(dev_fwd_r[rb], na, start, n, k, lv, Tf[0].sweep_nw, st, true, lo));
+                    SG_HIP(sg::launch_sweep_batch(dev_fwd_r[rb], na, start, n, k, lv, Tf[0].sweep_nw, false, st, true, lo));
                 else
                     SG_HIP(sg::launch_ring_tiled_batch(dev_fwd_r[rb], na, start, n, k, lv, config, iso, lo, st));
                 fp ^= 1;
