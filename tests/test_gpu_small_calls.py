@@ -87,3 +87,24 @@ def test_set_tunings_stand():
         torch.cuda.synchronize()
         got[tb] = plan.profile()[1]
     assert got == {0: 6, 1: 40, 2: 20, 4: 10, 5: 8, 6: 7}
+
+
+@pytest.mark.parametrize("nrec", [1, 62, 66, 900])
+@pytest.mark.parametrize("tuning", [None, dict(variant=2, tile_x=128, tile_z=64, time_block=3)],
+                         ids=["default", "wide"])
+def test_gradient_with_few_and_many_nodes_per_tile(nrec, tuning):
+    """Receiver nodes per tile on both sides of what the adjoint sums up before
+    its first level (256), repeated positions among them."""
+    rng = np.random.default_rng(nrec)
+    nz, nx, nt = 40, 60, 50
+    g = Geometry(nz=nz, nx=nx, dz=10.0, dx=10.0, dt=1e-3, nt=nt, nbl=8, vmax_hint=3000.0)
+    v = rng.uniform(1800.0, 3000.0, (nz, nx)).astype(np.float32)
+    src = np.array([[200.0, 300.0], [120.0, 250.0]])
+    rec = np.stack([rng.uniform(0, (nz - 1) * 10.0, nrec), rng.uniform(0, (nx - 1) * 10.0, nrec)], 1)
+    rec[nrec // 2:nrec // 2 + 2] = rec[0]
+    wl = oracle.ricker(40.0, g.dt, nt, t0=0.012)
+    resid = rng.standard_normal((2, g.nrow, nrec)).astype(np.float32)
+    ref = oracle.gradient(_og(g), v.astype(np.float64), src, wl, rec, resid.astype(np.float64))
+    got, _ = gpu_gradient(g, v, src, rec, wl, resid, ckpt=12, tuning=tuning)
+    assert np.linalg.norm(ref) > 0
+    assert rel_l2(got, ref) <= 1e-4
