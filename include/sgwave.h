@@ -559,9 +559,10 @@ sg_status sg_fault(const float *v, int32_t nz, int32_t ny, int32_t nx, double dz
 /* Faults applied one after another (a primary and its subsidiaries, App. B
  * Fault prose): out = fault[n-1](... fault[0](v)), each as sg_fault; ws a
  * second device volume [nz][ny][nx] (NULL allowed when nfaults <= 1), v, out
- * and ws pairwise disjoint.  The steps alternate between out and ws; a fault
- * whose reach is a box inside the volume costs that box plus a copy of the
- * previous fault's box (never the whole volume after the second step).
+ * and ws pairwise disjoint.  A fault whose reach is a box inside the volume
+ * costs that box and a copy of it (and the whole volume is copied once, for the
+ * first fault); one that reaches everywhere moves the state from one of out and
+ * ws to the other.
  * nfaults in 0..100000 (0 copies v).  A rough fault synchronises `stream`
  * once, as in sg_fault.  Errors as sg_fault, plus SG_EINVAL for overlapping
  * buffers or a missing ws. */

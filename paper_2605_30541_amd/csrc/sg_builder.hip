@@ -1134,38 +1134,41 @@ hipError_t copy_box(const T *src, int ny, int nx, const VoxBox &B, T *dst, hipSt
     return hipGetLastError();
 }
 
-// The faults in order, alternating between out and ws so the last lands in
-// out.  Step k writes dst_k, which holds the state of step k-2 (garbage for
-// k < 2); that state differs from step k-1's only on the box fault k-1
-// wrote, so that box is copied over first (the whole volume for k < 2) when
-// fault k does not cover the volume itself; then fault k runs on its box.
+// The faults in order.  The volume's state lies in one of out and ws; a fault
+// that covers the whole volume writes the other one, which then holds the
+// state, and one that changes a box writes that box of the other and has it
+// copied back.  The first fault reads v itself and writes the buffer from
+// which the whole-volume faults to come lead to out (with the rest of v copied
+// over first when it changes a box).  Alternating for every fault took a
+// second copy of the volume: 4.03 ms against 3.75 for 17 faults in 412 x 667 x
+// 667 voxels, 0.27 ms a copy.
 template <typename T, typename Launch>
 hipError_t fault_sequence(const T *v, int nz, int ny, int nx, const FaultFrame *F, int n, T *out, T *ws,
                           hipStream_t st, Launch run_kernel)
 {
-    const VoxBox whole{0, 0, 0, nz, ny, nx};
     const size_t bytes = (size_t)nz * ny * nx * sizeof(T);
-    if (n == 0) return hipMemcpyAsync(out, v, bytes, hipMemcpyDeviceToDevice, st);
-    const T *src = v;
-    VoxBox prev{};
-    bool prev_run = false;
-    for (int k = 0; k < n; ++k) {
-        T *dst = ((n - 1 - k) % 2 == 0) ? out : ws;
-        VoxBox B;
-        const bool run = fault_box(F[k], nz, ny, nx, B);
-        const bool partial = !run || B.bz < nz || B.by < ny || B.bx < nx;
+    auto whole = [&](const VoxBox &B) { return B.bz == nz && B.by == ny && B.bx == nx; };
+    VoxBox B;
+    int first = 0, flips = 0;   // the first fault that meets the volume; the whole-volume ones after it
+    while (first < n && !fault_box(F[first], nz, ny, nx, B)) ++first;
+    if (first == n) return hipMemcpyAsync(out, v, bytes, hipMemcpyDeviceToDevice, st);
+    for (int k = first + 1; k < n; ++k)
+        if (fault_box(F[k], nz, ny, nx, B) && whole(B)) ++flips;
+    T *cur = flips % 2 ? ws : out, *other = flips % 2 ? out : ws;
+    for (int k = first; k < n; ++k) {
+        if (!fault_box(F[k], nz, ny, nx, B)) continue;
         hipError_t e = hipSuccess;
-        if (partial) {
-            if (k < 2)
-                e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, st);
-            else if (prev_run)
-                e = copy_box(src, ny, nx, prev, dst, st);
+        if (k == first) {
+            if (!whole(B)) e = hipMemcpyAsync(cur, v, bytes, hipMemcpyDeviceToDevice, st);
+            if (e == hipSuccess) e = run_kernel(v, B, F[k], cur);
+        } else {
+            e = run_kernel(cur, B, F[k], other);
+            if (whole(B))
+                std::swap(cur, other);
+            else if (e == hipSuccess)
+                e = copy_box((const T *)other, ny, nx, B, cur, st);
         }
         if (e != hipSuccess) return e;
-        if (run && (e = run_kernel(src, B, F[k], dst)) != hipSuccess) return e;
-        prev = run ? B : whole;
-        prev_run = run;
-        src = dst;
     }
     return hipSuccess;
 }
