@@ -1899,41 +1899,48 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
         }
         sg::BatchItem *const dev_fwd = dev_fwd_r[0];
         // forward with checkpoints (no outputs): launches end at every
-        // checkpoint level and write it in place, where the next one reads it
+        // checkpoint level and write it in place, where the next one reads it.
+        // The last two segments, which the adjoint comes to first, leave their
+        // second time differences in the two rings on the way: they need no
+        // recompute (four slices of 20 shots, four segments of 50 levels: 92.6
+        // -> 87.9 ms).
+        const int nseg = Ls[0].nseg;
+        auto advance = [&](int n, int k, sg::LevelPair lv, int ring_of) {
+            if (ring_of < 0)
+                return sweep_fwd ? sg::launch_sweep_batch(dev_fwd, na, start, n, k, lv, Tf[0].sweep_nw, false, st)
+                                 : sg::launch_step_tiled_batch(dev_fwd, na, start, n, k, lv, config, iso, st);
+            sg::BatchItem *const dev = dev_fwd_r[ring_of & 1];
+            return sweep_fwd
+                       ? sg::launch_sweep_batch(dev, na, start, n, k, lv, Tf[0].sweep_nw, false, st, true, ring_of * C)
+                       : sg::launch_ring_tiled_batch(dev, na, start, n, k, lv, config, iso, ring_of * C, st);
+        };
         int pair = 0;
         for (int n = 0; n < nt - 1;) {
             const int k = std::min(std::min(tf.time_block, nt - 1 - n), C - n % C);
             sg::LevelPair lv{pair};
             if (n % C == 0) lv.in_ck = n / C;
             if ((n + k) % C == 0) lv.out_ck = (n + k) / C;
-            if (sweep_fwd)
-                SG_HIP(sg::launch_sweep_batch(dev_fwd, na, start, n, k, lv, Tf[0].sweep_nw, false, st));
-            else
-                SG_HIP(sg::launch_step_tiled_batch(dev_fwd, na, start, n, k, lv, config, iso, st));
+            SG_HIP(advance(n, k, lv, n / C >= nseg - 2 ? n / C : -1));
             pair ^= 1;
             n += k;
         }
-        // segments backwards: recompute into the segment's ring, then the
+        // segments backwards: recompute into the segment's ring (but the last two), then the
         // adjoint; its partial sums are folded on the side stream while the
         // next segment runs on the other ring
         sg_plan *p0 = items[act[0]].plan;
         if ((rc = side_stream(p0)) != SG_OK) return rc;
         bool folding[2] = {false, false};
         int mpair = 0;
-        const int nseg = Ls[0].nseg;
         for (int j = nseg - 1; j >= 0; --j) {
             const int lo = j * C, hi = std::min((j + 1) * C - 1, nt - 1), last = std::min(hi + 1, nt - 1);
             const int rb = j & 1;
             if (folding[rb]) SG_HIP(hipStreamWaitEvent(st, p0->ev_fold[rb], 0));
             int fp = 0;
-            for (int n = lo; n < last;) {
+            for (int n = lo; n < last && j < nseg - 2;) {
                 const int k = std::min(tf.time_block, last - n);
                 sg::LevelPair lv{fp};
                 if (n == lo) lv.in_ck = j;
-                if (sweep_fwd)
-                    SG_HIP(sg::launch_sweep_batch(dev_fwd_r[rb], na, start, n, k, lv, Tf[0].sweep_nw, false, st, true, lo));
-                else
-                    SG_HIP(sg::launch_ring_tiled_batch(dev_fwd_r[rb], na, start, n, k, lv, config, iso, lo, st));
+                SG_HIP(advance(n, k, lv, j));
                 fp ^= 1;
                 n += k;
             }
