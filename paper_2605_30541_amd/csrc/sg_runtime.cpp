@@ -441,11 +441,13 @@ size_t table_bytes(const sg_plan *p, int nshot, int nrec, int ckpt)
 // workspace: filled in the plan's next staging slot, copied on `st`.  A slot
 // smaller than the tables grows (one pinned allocation) unless `may_alloc`
 // is false, which gives SG_ENOSPACE instead.  `T` (may be null) gives the
-// tiling whose per-tile receiver lists are built.
-sg_status upload_tables(sg_plan *p, const Layout &L, char *ws, const sg_shots *sh, const sg::Tiling *T,
-                        hipStream_t st, bool may_alloc = true)
+// tiling whose per-tile receiver lists are built, and with `adjoint` the
+// adjoint's injection tables (their offsets in L move together).
+sg_status upload_tables(sg_plan *p, Layout &L, char *ws, const sg_shots *sh, const sg::Tiling *T, hipStream_t st,
+                        bool may_alloc = true, bool adjoint = false)
 {
     const size_t bytes = L.tables_end - L.gx;
+    size_t used = (L.inj_cap > 0 ? L.inj_tile : L.tables_end) - L.gx;   // bytes to copy
     std::lock_guard<std::mutex> lock(p->mu);
     StageSlot &slot = p->stage[p->stage_next];
     if (slot.bytes < bytes || !slot.done) {
@@ -461,7 +463,7 @@ sg_status upload_tables(sg_plan *p, const Layout &L, char *ws, const sg_shots *s
     p->stage_next = (p->stage_next + 1) % kStageSlots;
     char *h = (char *)slot.buf;
     auto at = [&](size_t off) { return h + (off - L.gx); };
-    std::memset(h, 0, bytes);
+    std::memset(h, 0, used);
     std::memcpy(at(L.gx), p->gx.data(), p->gx.size() * sizeof(float));
     std::memcpy(at(L.gz), p->gz.data(), p->gz.size() * sizeof(float));
     const double inv_cell = 1.0 / (p->g.dx * p->g.dz);
@@ -522,54 +524,81 @@ sg_status upload_tables(sg_plan *p, const Layout &L, char *ws, const sg_shots *s
                 std::stable_sort(list + start[q], list + start[q + 1],
                                  [](const sg::RecEntry &a, const sg::RecEntry &b) { return a.lds < b.lds; });
     }
-    if (T && L.inj_cap > 0) {
+    if (T && adjoint && L.inj_cap > 0) {
         // adjoint residual injection: receiver nodes inside each tile's loaded
-        // region, grouped by cell in a fixed order
+        // region, grouped by cell in a fixed order.  The tables' room is for the
+        // finest tiling (81 regions a node, 7 MB for 900 receivers); they are
+        // laid out tight, and only what they fill is written and copied (with
+        // all of it, and a search of every receiver for every tile, a plan's
+        // gradient took 2.5 ms on the host before its first launch).
         const int tiles = T->ntx * T->ntz, LW = T->ex + 2 * sg::kHalo, halo = sg::kHalo * T->tb;
         const bool free_top = p->g.top == SG_TOP_FREE;
-        std::vector<Nodes> rn(std::max(sh->nrec, 0));
-        for (int i = 0; i < sh->nrec; ++i) bilinear(p, sh->rec_zx[2 * i], sh->rec_zx[2 * i + 1], 1.0, &rn[i]);
+        auto tile_z0 = [&](int tzi) {
+            return free_top ? (tzi == 0 ? -T->k : T->tz_top + (tzi - 1) * T->tz - halo) : tzi * T->tz - halo;
+        };
+        auto tile_x0 = [&](int txi) { return txi * T->tx - halo; };
+        std::vector<std::vector<std::pair<int64_t, std::pair<int32_t, float>>>> hits(tiles);
+        for (int r = 0; r < sh->nrec; ++r) {
+            bilinear(p, sh->rec_zx[2 * r], sh->rec_zx[2 * r + 1], 1.0, &nd);
+            for (int q = 0; q < sg::kNodes; ++q) {
+                if (nd.w[q] == 0.f) continue;
+                const int iz = nd.iz[q], ix = nd.ix[q];
+                for (int tzi = 0; tzi < T->ntz; ++tzi) {
+                    if (iz < tile_z0(tzi) || iz >= tile_z0(tzi) + T->ez) continue;
+                    for (int txi = 0; txi < T->ntx; ++txi)
+                        if (ix >= tile_x0(txi) && ix < tile_x0(txi) + T->ex)
+                            hits[tzi * T->ntx + txi].push_back({(int64_t)iz * p->Nx + ix, {r, nd.w[q]}});
+                }
+            }
+        }
+        size_t ncell = 0, npair = 0;
+        for (auto &tile : hits) {
+            std::stable_sort(tile.begin(), tile.end(),
+                             [](const auto &a, const auto &b) { return a.first < b.first; });
+            npair += tile.size();
+            for (size_t q = 0; q < tile.size(); ++q) ncell += q == 0 || tile[q].first != tile[q - 1].first;
+        }
+        if ((int64_t)npair > L.inj_cap) return fail(SG_EINVAL, "receiver injection tables overflow");
+        size_t o = L.inj_lds;
+        auto take = [&](size_t n) {
+            const size_t a = o;
+            o = align_up(o + n * 4, 256);
+            return a;
+        };
+        L.inj_lds = take(ncell);
+        L.inj_iz = take(ncell);
+        L.inj_ix = take(ncell);
+        L.inj_pstart = take(ncell + 1);
+        L.inj_rid = take(npair);
+        L.inj_w = take(npair);
+        used = std::min(o, L.tables_end) - L.gx;
         int32_t *tstart = (int32_t *)at(L.inj_tile), *clds = (int32_t *)at(L.inj_lds);
         int32_t *ciz = (int32_t *)at(L.inj_iz), *cix = (int32_t *)at(L.inj_ix);
         int32_t *cps = (int32_t *)at(L.inj_pstart), *prid = (int32_t *)at(L.inj_rid);
         float *pw = (float *)at(L.inj_w);
-        int64_t ncell = 0, npair = 0;
-        std::vector<std::pair<int64_t, std::pair<int32_t, float>>> hits;
+        int32_t c = 0, pr = 0;
         for (int tile = 0; tile < tiles; ++tile) {
-            const int tzi = tile / T->ntx, txi = tile % T->ntx;
-            const int ez0 = free_top ? (tzi == 0 ? -T->k : T->tz_top + (tzi - 1) * T->tz - halo) : tzi * T->tz - halo;
-            const int ex0 = txi * T->tx - halo;
-            hits.clear();
-            for (int r = 0; r < sh->nrec; ++r)
-                for (int q = 0; q < sg::kNodes; ++q) {
-                    if (rn[r].w[q] == 0.f) continue;
-                    const int iz = rn[r].iz[q], ix = rn[r].ix[q];
-                    if (iz >= ez0 && iz < ez0 + T->ez && ix >= ex0 && ix < ex0 + T->ex)
-                        hits.push_back({(int64_t)iz * p->Nx + ix, {r, rn[r].w[q]}});
+            const int ez0 = tile_z0(tile / T->ntx), ex0 = tile_x0(tile % T->ntx);
+            const auto &hit = hits[tile];
+            tstart[tile] = c;
+            for (size_t q = 0; q < hit.size(); ++q) {
+                if (q == 0 || hit[q].first != hit[q - 1].first) {
+                    const int iz = (int)(hit[q].first / p->Nx), ix = (int)(hit[q].first % p->Nx);
+                    ciz[c] = iz;
+                    cix[c] = ix;
+                    clds[c] = (iz - ez0 + sg::kHalo) * LW + (ix - ex0 + sg::kHalo);
+                    cps[c] = pr;
+                    ++c;
                 }
-            std::stable_sort(hits.begin(), hits.end(),
-                             [](const auto &a, const auto &b) { return a.first < b.first; });
-            tstart[tile] = (int32_t)ncell;
-            for (size_t q = 0; q < hits.size(); ++q) {
-                if (q == 0 || hits[q].first != hits[q - 1].first) {
-                    if (ncell >= L.inj_cap) return fail(SG_EINVAL, "receiver injection tables overflow");
-                    const int iz = (int)(hits[q].first / p->Nx), ix = (int)(hits[q].first % p->Nx);
-                    ciz[ncell] = iz;
-                    cix[ncell] = ix;
-                    clds[ncell] = (iz - ez0 + sg::kHalo) * LW + (ix - ex0 + sg::kHalo);
-                    cps[ncell] = (int32_t)npair;
-                    ++ncell;
-                }
-                if (npair >= L.inj_cap) return fail(SG_EINVAL, "receiver injection tables overflow");
-                prid[npair] = hits[q].second.first;
-                pw[npair] = hits[q].second.second;
-                ++npair;
+                prid[pr] = hit[q].second.first;
+                pw[pr] = hit[q].second.second;
+                ++pr;
             }
         }
-        tstart[tiles] = (int32_t)ncell;
-        cps[ncell] = (int32_t)npair;
+        tstart[tiles] = c;
+        cps[c] = pr;
     }
-    SG_HIP(hipMemcpyAsync(ws + L.gx, h, bytes, hipMemcpyHostToDevice, st));
+    SG_HIP(hipMemcpyAsync(ws + L.gx, h, used, hipMemcpyHostToDevice, st));
     SG_HIP(hipEventRecord(slot.done, st));
     slot.pending = true;
     return SG_OK;
@@ -1421,7 +1450,7 @@ sg_status sg_adjoint_gradient(sg_plan *p, const float *vp, const sg_shots *shots
     if (rc != SG_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     char *w = (char *)ws;
-    if ((rc = upload_tables(p, c.L, w, shots, &c.T, st)) != SG_OK) return rc;
+    if ((rc = upload_tables(p, c.L, w, shots, &c.T, st, true, true)) != SG_OK) return rc;
     sg::SliceDesc s = describe(p, c.L, w, shots, nullptr, nullptr);
     SG_HIP(sg::launch_prepare(s, vp, (float)(p->g.dt * p->g.dt), st));
     const int nshot = shots->nshot, nt = p->g.nt;
@@ -1824,11 +1853,11 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
             act.push_back(i);
             views.push_back(shots_view(it.shots, s0, cnt, nt));
             const sg_shots *sv = &views.back();
-            const Layout L = layout_of(it.plan, cnt, it.shots->nrec, C);
+            Layout L = layout_of(it.plan, cnt, it.shots->nrec, C);
             Ls.push_back(L);
             char *wi = w + o;
             o += region;
-            if ((rc = upload_tables(it.plan, L, wi, sv, &T[i], st)) != SG_OK) return rc;
+            if ((rc = upload_tables(it.plan, L, wi, sv, &T[i], st, true, true)) != SG_OK) return rc;
             sg::BatchItem b{};
             b.s = describe(it.plan, L, wi, sv, nullptr, nullptr);
             for (int m = 1; m <= sg::kHalo; ++m) iso = iso && b.s.cz[m] == b.s.cx[m];
