@@ -5,8 +5,8 @@
 // sinc (beta 6, weights normalised to sum 1, taps clamped to the axis).
 // Volumes are [nz][ny][nx], x fastest.
 //
-// Deposit: one thread per (y, x) column of the band; the column's contacts in
-// FP64 in LDS, the texture noise in FP64.
+// Deposit: four waves per 64 (y, x) columns of the band; the columns' contacts
+// sorted in FP64 in LDS, the texture noise in FP64.
 // Squish: one thread per (y, x) column.  The shift is constant down a column,
 // so the 8 weights are computed once and the column streams through registers
 // in blocks of 8 rows: one load and 8 FMAs per voxel (HBM-bound, 8 B per voxel
@@ -448,9 +448,9 @@ __device__ inline void fault_pull_quad(const float *__restrict__ v, int nz, int 
 // weights and two row groups): rows in groups of 4 left room for two and took
 // 4.83 ms against 4.08 (412 x 667 x 667 voxels, one fault through 31 % of them and
 // 16 small ones, copies included; 6.34 ms one voxel at a time, and 6.16 with the
-// cheaper weights and source alone, which left it bound by the L1).  Bricks go to the XCDs in groups of kSbGroup x kSbGroup
-// bricks (y, z), so the source rows that neighbouring bricks share are
-// fetched into one L2.
+// cheaper weights and source alone, which left it bound by the L1).  Bricks go
+// to the XCDs in groups of kSbGroup x kSbGroup bricks (y, z), so the source rows
+// that neighbouring bricks share are fetched into one L2.
 constexpr int kSbZ = 4, kSbY = 4, kSbPer = kSbZ * kSbY / 4, kSbGroup = 4;
 
 struct BrickGrid {
@@ -470,8 +470,9 @@ inline int64_t brick_blocks(const VoxBox &B)
     return (ngroup + 7) / 8 * 8 * (kSbGroup * kSbGroup);
 }
 
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_fault(const float *__restrict__ v, int nz, int ny, int nx, VoxBox B,
-                                               BrickGrid G, FaultFrame F, float fill, float *__restrict__ out)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+k_fault(const float *__restrict__ v, int nz, int ny, int nx, VoxBox B, BrickGrid G, FaultFrame F, float fill,
+        float *__restrict__ out)
 {
     __shared__ FaultTaps ptap[kSbPer][256];   // the taps of each thread's moved voxels
     __shared__ uint8_t quads[256];            // threads whose voxels are pulled together
