@@ -225,3 +225,26 @@ def test_box_word_and_block_edges_match_the_oracle(shape, h, frac, amp):
     assert 0 < K.sum() < K.size
     assert np.array_equal(mask, K)
     assert np.array_equal(got, ref.astype(np.float32))
+
+
+@pytest.mark.parametrize("value,amp", [(np.inf, 0.2), (-np.inf, 0.2), (np.inf, -0.2), (3e38, 0.2), (None, 1e200),
+                                       (None, -1e200), (None, 1e300), (None, 1e152)])
+def test_fields_and_amplitudes_whose_square_overflows(value, amp):
+    """Field values of +-infinity (in a block beside the body, past its rows y,
+    and in one inside it) and finite products a rbar xi whose square overflows:
+    phi' is decided by the sign of the field wherever the distance is finite."""
+    shape, h = (24, 30, 70), (10.0, 10.0, 10.0)
+    V = _model(shape, 41)
+    grf = _field(1, shape, 2.0, 42)
+    if value is not None:
+        grf[0, 10:16, 22:28, 50:60] = value
+        grf[0, 9:15, 8:13, 25:35] = value
+    c, r = [(120.0, 100.0, 300.0)], [(60.0, 50.0, 100.0)]
+    for rot in (np.eye(3), _rot(0.4, -0.3, 0.8)):
+        got, mask, ref, K = _run(V, h, c, r, [rot], grf, amp, 4500.0, 0.0, 2)
+        _report("square overflows, field %s, amplitude %g" % (value, amp), mask, K)
+        assert 0 < K.sum() < K.size
+        if value is not None and value * amp > 0:
+            assert K[11:15, 23:27, 51:59].all()     # the block past the body's rows
+        assert np.array_equal(mask, K)
+        assert np.array_equal(got, ref.astype(np.float32))
