@@ -45,13 +45,15 @@ __device__ inline double wavenumber2(int i, int n, double l)
 // q^-half_p for q >= 1: log2 q = e + log2 m with q = m 2^e, the
 // product with half_p in FP64, of which only the fraction goes through the
 // FP32 exponential.  (FP32 throughout, the rounding of log2 q ~ 14 alone
-// moved the field by 1e-7 of its norm.)
+// moved the field by 1e-7 of its norm.)  A q beyond FP64 (infinite, from
+// lengths past 1e153 cells) gives 0, or 1 where half_p is 0; exponents past
+// 1000, infinite ones among them, give 0.
 __device__ inline float spectral_amp(double q, double half_p)
 {
     int e;
     const float m = (float)frexp(q, &e);   // in [1/2, 1)
-    const double s = half_p * ((double)e + (double)log2f(m)), n = rint(s);
-    return ldexpf(exp2f((float)(n - s)), -(int)fmin(n, 1000.0));
+    const double s = half_p > 0.0 ? fmin(half_p * ((double)e + (double)log2f(m)), 1000.0) : 0.0, n = rint(s);
+    return ldexpf(exp2f((float)(n - s)), -(int)n);
 }
 
 // Where the half spectrum lives: row (z, y) of Px/2 + 1 values starts at z *

@@ -89,3 +89,18 @@ def test_grf_at_every_line_length(shape):
     e = rel_l2(got, ref)
     print("%s: rel-L2 %.2e" % (shape, e), flush=True)
     assert e <= 2e-6
+
+
+@pytest.mark.parametrize("ell,p", [((1e160, 0.8, 1.3), 2.0), ((0.8, 1e300, 0.6), 1.0), ((1.3, 0.8, 1e155), 3.0),
+                                   ((1e200, 1e200, 0.6), 2.0), ((1e100, 0.8, 0.6), 2.0), ((1e200, 0.8, 0.6), 0.0)])
+def test_grf_of_lengths_whose_square_overflows(ell, p):
+    """Any finite correlation length is accepted.  Where (k l)^2 overflows FP64
+    the spectral factor is 0 (1 when p is 0, white noise), so the field is
+    constant along that axis; bound as for the other short lengths."""
+    import torch
+    shape = (13, 16, 27)
+    noise = _noise(shape, 11)
+    got = sgwave.grf(torch.from_numpy(noise).cuda(), shape, ell, p).cpu().numpy()
+    with np.errstate(over="ignore"):
+        ref = OB.grf(noise.astype(np.float64), shape, ell, p)
+    assert np.isfinite(got).all() and rel_l2(got, ref) <= 2e-6
