@@ -5,8 +5,8 @@
 // sinc (beta 6, weights normalised to sum 1, taps clamped to the axis).
 // Volumes are [nz][ny][nx], x fastest.
 //
-// Deposit: four waves per 64 (y, x) columns of the band; the columns' contacts
-// sorted in FP64 in LDS, the texture noise in FP64.
+// Deposit: one or four waves per 64 (y, x) columns of the band; the columns'
+// contacts in order in FP64 in LDS (up to 64 KB), the texture noise in FP64.
 // Squish: one thread per (y, x) column.  The shift is constant down a column,
 // so the 8 weights are computed once and the column streams through registers
 // in blocks of 8 rows: one load and 8 FMAs per voxel (HBM-bound, 8 B per voxel
@@ -30,7 +30,7 @@ constexpr int kTaps = 8;
 // four floats at any 4-byte-aligned address (one 16-byte load)
 typedef float Float4u __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kBrickZ = 16, kBrickY = 16, kBrickRows = kBrickZ * kBrickY;   // fault kernel
-constexpr int kDepositThreads = 256;   // 64 columns, four waves; the contacts fill up to 64 KB of LDS
+constexpr int kDepthsPerPass = 6;   // Deposit: one pass to put the contacts in order for so many depths of a run
 
 // Normalised weights of the taps floor(s)-3 .. floor(s)+4 for the fractional
 // part f = s - floor(s): tap j sits at t = f + 3 - j from the sample and
@@ -717,23 +717,29 @@ __global__ void __launch_bounds__(256) k_simplex3d(const int32_t *__restrict__ p
 }
 
 // Deposit (Alg. 1, boundary path): a workgroup takes 64 (y, x) columns of the
-// band [t][ny][nx] and a run of its depths, each of its waves a quarter of the
+// band [t][ny][nx] and a run of its depths, each of its waves a part of the
 // run.  The contacts are the cumulative bed thicknesses (summed in FP64 in bed
 // order), each moved by taper x a_B x its noise and clamped to the band; the
-// waves compute them into LDS (FP64, [contact][lane]) in turn, and one wave
-// sorts each column's (they are nearly in order).  A voxel's bed is the
-// number of contacts at or above it, starting at the deepest of those, so
-// walking down only looks at the next contact; the texture is sampled at the
-// depth below that start plus the bed's offset.  SIMPLEX: the contact noise is
-// simplex noise (perm_b) on the plane at the contact's mean depth and the
-// texture simplex noise (perm_t); else the contact noise is an input and the
-// texture value noise on a lattice.
+// waves compute them into LDS (FP64, [contact][lane]) in turn.  A voxel's bed
+// is the number of contacts at or above it, starting at the deepest of those,
+// so with the contacts in order, walking down only looks at the next one.  They
+// are nearly in order where beds are thicker than the noise moves them, and a
+// few passes of exchanges between neighbours finish it.  Contacts that are not
+// in order after one pass for every kDepthsPerPass depths of the run (thin bands
+// of many beds) are all looked at for every voxel instead: the passes given up
+// cost a third of that at most.  The texture is sampled at the depth below the
+// bed's start plus the bed's offset.  SIMPLEX: the contact noise is simplex
+// noise (perm_b) on the plane at the contact's mean depth and the texture
+// simplex noise (perm_t); else the contact noise is an input and the texture
+// value noise on a lattice.
 // Bound by FP64 vector issue (about 200 operations a voxel with simplex
 // texture).  One thread per whole column, all contacts looked at for every
-// voxel, left two waves per SIMD (LDS) and took 7.29 ms for a 200 x 1000 x
-// 1000 band of 40 beds with simplex noise; this form 1.47 ms.
-template <bool SIMPLEX>
-__global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, int run, float *__restrict__ out)
+// voxel, left two waves per SIMD (LDS) and took 7.17 ms for a 200 x 1000 x
+// 1000 band of 40 beds with simplex noise; this form 1.41 ms.  10 depths of 120
+// beds with value noise, whose contacts cross 40 others: 1.97 ms that way, 9.84
+// with one wave sorting each column's by insertion, 1.10 in this form.
+template <bool SIMPLEX, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) k_deposit(DepositArgs A, int run, float *__restrict__ out)
 {
     extern __shared__ double hcol[];   // [nbeds - 1][64]
     __shared__ int Pb[SIMPLEX ? 256 : 1], Pt[SIMPLEX ? 256 : 1];
@@ -742,7 +748,7 @@ __global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, int 
         load_perm(A.perm_t, Pt);
     }
     const int64_t plane = (int64_t)A.ny * A.nx;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t col0 = (int64_t)blockIdx.x * 64 + lane, col = min(col0, plane - 1);
     const int iy = (int)(col / A.nx), ix = (int)(col - (int64_t)iy * A.nx);
     const double t = A.t;
@@ -776,31 +782,51 @@ __global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, int 
     }
     const int nc = A.nbeds - 1;
     {
-        double H = 0.0;
-        for (int i = 0; i < nc; ++i) {
-            H += (double)A.thick[i];
-            if (i % (kDepositThreads / 64) != wv) continue;
-            const double eta =
-                SIMPLEX ? simplex3(Pb, H * A.dz / A.lam_b[0], by, bx) : (double)A.eta_b[(int64_t)i * plane + col];
+        double H = 0.0;   // the thicknesses' sum up to contact i
+        auto contact = [&](int i, double eta) {
             hcol[i * 64 + lane] = fmin(fmax(H + tau(H) * A.a_B * eta, 0.0), t - 1.0);
+        };
+        if constexpr (SIMPLEX) {
+            for (int i = 0; i < nc; ++i) {
+                H += (double)A.thick[i];
+                if (i % WAVES == wv) contact(i, simplex3(Pb, H * A.dz / A.lam_b[0], by, bx));
+            }
+        } else {
+            // the thicknesses lie in the wave's lanes, so that only the noise is waited for
+            const float lo = lane < nc ? A.thick[lane] : 0.f, hi = 64 + lane < nc ? A.thick[64 + lane] : 0.f;
+            auto bed = [&](int k) {
+                return (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(k < 64 ? lo : hi), k & 63));
+            };
+            for (int k = 0; k <= wv; ++k) H += bed(k);
+            for (int i = wv; i < nc; i += WAVES) {
+                contact(i, (double)A.eta_b[(int64_t)i * plane + col]);
+#pragma unroll
+                for (int w = 1; w <= WAVES; ++w) H += bed(i + w);   // (past the last bed: unused)
+            }
         }
     }
     __syncthreads();
-    if (wv == 0)
-        for (int i = 1; i < nc; ++i) {   // insertion sort, ascending
-            const double h = hcol[i * 64 + lane];
-            int q = i;
-            for (; q > 0; --q) {
-                const double g = hcol[(q - 1) * 64 + lane];
-                if (g <= h) break;
-                hcol[q * 64 + lane] = g;
-            }
-            if (q < i) hcol[q * 64 + lane] = h;
-        }
-    __syncthreads();
-    if (col0 >= plane) return;
     const int b0 = (int)blockIdx.y * run, b1 = min(A.t, b0 + run);   // the workgroup's depths
-    const int part = (b1 - b0 + kDepositThreads / 64 - 1) / (kDepositThreads / 64);
+    // ascending order by exchanges between neighbours, the waves taking the pairs in turn
+    bool in_order = nc < 2;
+    for (int pass = (b1 - b0) / kDepthsPerPass; !in_order && pass > 0; --pass) {
+        int moved = 0;
+#pragma unroll
+        for (int odd = 0; odd < 2; ++odd) {
+            for (int i = odd + 2 * wv; i + 1 < nc; i += 2 * WAVES) {
+                const double g = hcol[i * 64 + lane], h = hcol[(i + 1) * 64 + lane];
+                if (g > h) {
+                    hcol[i * 64 + lane] = h;
+                    hcol[(i + 1) * 64 + lane] = g;
+                    moved = 1;
+                }
+            }
+            if (odd == 0) __syncthreads();
+        }
+        in_order = !__syncthreads_or(moved);
+    }
+    if (col0 >= plane) return;
+    const int part = (b1 - b0 + WAVES - 1) / WAVES;
     const int z0w = b0 + wv * part, z1w = min(b1, z0w + part);
     const double none = INFINITY;   // (no further contact)
     int bed = 0;
@@ -808,7 +834,19 @@ __global__ void __launch_bounds__(kDepositThreads) k_deposit(DepositArgs A, int 
     double off = (double)A.tex_off[0], dv = (double)A.vbed[0] - vbar;
     for (int iz = z0w; iz < z1w; ++iz) {
         const double z = iz;
-        if (next <= z) {
+        if (!in_order) {
+            bed = 0;
+            start = 0.0;
+            for (int i = 0; i < nc; ++i) {
+                const double h = hcol[i * 64 + lane];
+                if (h <= z) {
+                    ++bed;
+                    start = fmax(start, h);
+                }
+            }
+            off = (double)A.tex_off[bed];
+            dv = (double)A.vbed[bed] - vbar;
+        } else if (next <= z) {
             do {
                 start = next;
                 ++bed;
@@ -948,10 +986,15 @@ hipError_t launch_deposit(const DepositArgs &A, float *out, hipStream_t st)
     // div_by takes lengths and depths far from the ends of the FP64 range
     const double big = 0x1p200, lam = A.lam_t[0];
     B.exact_div = A.simplex && !(lam > 1.0 / big && lam < big && A.dz > 1.0 / big && A.dz < big);
-    if (A.simplex)
-        hipLaunchKernelGGL(k_deposit<true>, grid, dim3(kDepositThreads), lds, st, B, run, out);
-    else
-        hipLaunchKernelGGL(k_deposit<false>, grid, dim3(kDepositThreads), lds, st, B, run, out);
+    // One wave a workgroup where a thin band of few beds has columns enough to
+    // fill the chip: the set-up, which every wave repeats, is then most of the
+    // work.  1000 x 1000 columns with value noise, one wave against four: 4 depths
+    // of 10 beds 43.6 and 61.1 us, 4 of 20 75.6 and 80.5, 16 of 10 140 and 141, 4 of
+    // 40 186 and 120; with simplex noise 4 of 10 109 and 115, 4 of 20 208 and 187.
+    const int waves = A.t <= 8 && A.nbeds <= (A.simplex ? 12 : 24) && A.t * A.nbeds <= 100 && cols >= 4096 ? 1 : 4;
+    auto *kernel = A.simplex ? (waves == 1 ? k_deposit<true, 1> : k_deposit<true, 4>)
+                             : (waves == 1 ? k_deposit<false, 1> : k_deposit<false, 4>);
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), lds, st, B, run, out);
     return hipGetLastError();
 }
 

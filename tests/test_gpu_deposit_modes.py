@@ -120,3 +120,68 @@ def test_deposit_at_the_edges_of_columns_and_depth_runs(form, t, ny, nx, nb, a_B
     e = rel_l2(got, ref)
     print("%s %s: rel-L2 %.2e" % (form, (t, ny, nx, nb), e), flush=True)
     assert e <= TOL
+
+
+def _value_band(t, ny, nx, nb, a_B, seed):
+    rng = np.random.default_rng(seed)
+    a = dict(thick=rng.uniform(0.3, 2.0, nb).astype(np.float32) * np.float32(t / nb),
+             vbed=rng.normal(2600.0, 150.0, nb).astype(np.float32), off=rng.uniform(0, 300, nb).astype(np.float32),
+             eta=rng.uniform(-1, 1, (max(nb - 1, 1), ny, nx)).astype(np.float32),
+             tex=rng.uniform(-1, 1, (5, 4, 6)).astype(np.float32))
+    d = {k: _dev(v) for k, v in a.items()}
+    run = lambda: sgwave.deposit(t, ny, nx, 5.0, 10.0, 12.5, d["thick"], d["vbed"], 0.4,  # noqa: E731
+                                 d["eta"] if nb > 1 else None, a_B, d["tex"], (35.0, 200.0, 260.0), d["off"], 50.0,
+                                 0.15, 0.2)
+    return a, run
+
+
+@pytest.mark.parametrize("form", ["simplex", "value"])
+@pytest.mark.parametrize("t,ny,nx,nb,a_B", [(2, 3, 70, 129, 50.0), (6, 2, 65, 40, 20.0), (13, 1, 130, 100, 60.0),
+                                            (36, 2, 64, 64, 3.0), (48, 1, 100, 3, 40.0), (12, 1, 66, 2, 5.0),
+                                            (3, 512, 513, 12, 2.0), (8, 512, 512, 5, 9.0)])
+def test_deposit_of_contacts_in_any_order(form, t, ny, nx, nb, a_B):
+    """Contacts that are in order after a pass or some, and far from it when
+    the passes end, bands of fewer depths than one pass is given for, and areas
+    wide enough for one wave a workgroup.  The bar of the other Deposit tests."""
+    seed = 1000 * t + nb
+    a, run = _value_band(t, ny, nx, nb, a_B, seed)
+    f64 = {k: v.astype(np.float64) for k, v in a.items()}
+    args = (t, ny, nx, 5.0, 10.0, 12.5)
+    if form == "simplex":
+        rng = np.random.default_rng(seed + 1)
+        pb, pt = rng.permutation(256), rng.permutation(256)
+        lam_b, lam_t = (0.7, 300.0, 240.0), (35.0, 200.0, 260.0)
+        got = _host(sgwave.deposit_simplex(*args, _dev(a["thick"]), _dev(a["vbed"]), 0.4, _dev(pb, np.int32), lam_b,
+                                           a_B, _dev(pt, np.int32), lam_t, _dev(a["off"]), 50.0, 0.15, 0.2))
+        ref = OB.deposit_simplex(*args, f64["thick"], f64["vbed"], 0.4, pb, lam_b, a_B, pt, lam_t, f64["off"], 50.0,
+                                 0.15, 0.2)
+    else:
+        got = _host(run())
+        ref = OB.deposit(*args, f64["thick"], f64["vbed"], 0.4, f64["eta"][:nb - 1], a_B, f64["tex"],
+                         (35.0, 200.0, 260.0), f64["off"], 50.0, 0.15, 0.2)
+    e = rel_l2(got, ref)
+    print("%s %s: rel-L2 %.2e" % (form, (t, ny, nx, nb), e), flush=True)
+    assert e <= TOL
+
+
+def test_contacts_out_of_order_cost_no_more_than_looking_at_all_of_them():
+    """120 beds in 10 depths: contacts that cross dozens of others against the
+    same band with none moved.  Looking at every contact for every depth is at
+    most about twice the work; a sort of each column's by one wave was seven
+    times."""
+    import torch
+
+    def fastest(run):
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            run()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    flat, crossed = (fastest(_value_band(10, 700, 700, 120, a_B, 5)[1]) for a_B in (0.0, 4.0))
+    print("in order %.3f ms, out of order %.3f ms" % (flat, crossed), flush=True)
+    assert crossed <= 4.0 * flat
