@@ -99,9 +99,10 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
     float *out_cur = out_prev + s.frame;
     const bool free_top = s.free_top != 0;
 
-    // rows holding source nodes of this shot (srow_lo and srow_hi, one below
-    // the other or the same) and this lane's node weight on each of them; the
-    // wavelet samples are read only there (level n+s takes w(t_{n+s-1}))
+    // rows holding source nodes of this shot in this strip's columns (srow_lo
+    // and srow_hi, one below the other or the same) and this lane's node weight
+    // on each of them; the wavelet samples are read only there (level n+s takes
+    // w(t_{n+s-1})).  Strips beside the source have none, and run plain steps.
     const float *wshot = s.wavelet + (int64_t)shot * s.wavelet_stride + t.n;
     int srow_lo = 1 << 30, srow_hi = -(1 << 30);
     float sw_lo = 0.f, sw_hi = 0.f;
@@ -113,6 +114,7 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
             iz[k] = gld(s.src_iz + shot * kNodes + k);
             ixn[k] = gld(s.src_ix + shot * kNodes + k);
             wn[k] = gld(s.src_w + shot * kNodes + k);
+            if (ixn[k] < ex0 || ixn[k] >= ex0 + EX) wn[k] = 0.f;
         }
 #pragma unroll
         for (int k = 0; k < kNodes; ++k)
@@ -201,11 +203,17 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
     issue(1, j0 + 1);
 
     // The plain steps: rows past the free top's ghost rows, no source row and no
-    // receiver sample among them.  Nearly all steps of a segment are plain, and
-    // what the others test for (mirror, sources, receivers, rows above the grid,
-    // with the scalar registers that spills) is a third of their instructions, so a group
+    // receiver sample among them or below them in the strip's segment.  What the
+    // others test for (mirror, sources, receivers, rows above the grid, with the
+    // scalar registers that spills) is a third of their instructions, so a group
     // of kQ plain steps runs in a form without it, and on strips and rows where
-    // every cell has a = 1 (UNIT) without loading 2a.
+    // every cell has a = 1 (UNIT) without loading 2a.  With sources and receivers
+    // near the surface nearly all steps are plain; a deep source keeps its own
+    // strip's segment in the general form down to it, deep receivers theirs.  16
+    // shots x 100 updates of 620 x 1001 cells (256-column strips, 160-row segments,
+    // time block 5), in the general form throughout and now: all at the surface
+    // 3.64 and 2.34 ms, sources at 92 % of the depth 3.76 and 2.72, receivers there
+    // 3.76 and 2.87, receivers down a vertical line 8.62 and 5.07.
     // byte offset of a row past the ghost rows; below the grid that of the last guard row
     auto rowp = [&](int R) -> uint32_t { return (uint32_t)((min(R, Nz + kGuard - 1) + kGuard) * pitch) * 4u + xo4; };
     auto plain_step = [&](auto ph, auto unit, const int j) {
@@ -275,22 +283,29 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
         Q[0][slot(PH)] = cin;
         my[slot(PH) * LW] = cin;
         if (free_top && j >= 1 && j <= kHalo) Q[0][slot(-PH)] = -cin;
-        // receivers of levels n..n+TB-1 at base row j - 4q - 6 (a loop, not
-        // unrolled: it touches no register queue, and copies of it in every
-        // phase and level took registers from the plain steps)
+        // receivers of levels n..n+TB-1 at base row j - 4q - 6: an entry's row
+        // tells its level, so each is looked at once a step and not once for
+        // every level (receivers down a vertical line, strips of the whole height,
+        // time block 5: 47.9 -> 22.3 ms).  A loop, not unrolled: it touches no
+        // register queue, and copies of it in every phase and level took registers
+        // from the plain steps.
         if (!RECOMP && j >= rec_j0 && j <= rec_j1) {
-#pragma unroll 1
+            bool any = false;
+#pragma unroll
             for (int q = 0; q < TB; ++q) {
                 const int Rb = j - 4 * q - 6;
-                if (!((due >> q) & 1u) || Rb < rrow_lo || Rb > rrow_hi) continue;
-                const int s0 = (PH + 8 * kQ - 4 * q - 6) % kQ, s1 = s0 + 1 == kQ ? 0 : s0 + 1;
-                const float *L0 = lds + q * RING + s0 * LW;
-                const float *L1 = lds + q * RING + s1 * LW;
-                float *row = s.gathers + ((int64_t)shot * s.nrow + (t.n + q) / s.rec_every) * s.nrec;
+                any |= ((due >> q) & 1u) && Rb >= rrow_lo && Rb <= rrow_hi;
+            }
+            if (any) {
+#pragma unroll 1
                 for (int e = rbeg + (int)threadIdx.x; e < rend; e += NTHR) {
-                    const int code = gld(&s.rec_list[e].lds);
-                    if (code / LW != Rb) continue;
-                    const int c = code - Rb * LW;
+                    const int code = gld(&s.rec_list[e].lds), Rb = code / LW, c = code - Rb * LW;
+                    const int d = j - 6 - Rb, q = d >> 2;
+                    if (d < 0 || (d & 3) || q >= TB || !((due >> q) & 1u)) continue;
+                    const int s0 = (PH + 8 * kQ - 4 * q - 6) % kQ, s1 = s0 + 1 == kQ ? 0 : s0 + 1;
+                    const float *L0 = lds + q * RING + s0 * LW;
+                    const float *L1 = lds + q * RING + s1 * LW;
+                    float *row = s.gathers + ((int64_t)shot * s.nrow + (t.n + q) / s.rec_every) * s.nrec;
                     const float w0 = gld(&s.rec_list[e].w[0]), w1 = gld(&s.rec_list[e].w[1]);
                     const float w2 = gld(&s.rec_list[e].w[2]), w3 = gld(&s.rec_list[e].w[3]);
                     row[gld(&s.rec_list[e].r)] = w0 * L0[c] + w1 * L0[c + 1] + w2 * L1[c] + w3 * L1[c + 1];
@@ -360,7 +375,9 @@ __device__ __forceinline__ void sweep_body(const SliceDesc &s, const TileArgs &t
     // to the last source row or receiver sample, or to the first row clear of
     // the ghost rows; the plain ones whose rows j - 4 TB .. j + 4 and columns
     // all have a = 1; the other plain ones, down to the guard rows.
-    const int jp0 = max(4 * TB + kHalo + 1, max(srow_hi + 4 * TB, rec_j1) + 1);
+    // (a source below the segment's last step is no source of the segment)
+    const int jsrc = srow_lo < j1 - 4 ? srow_hi + 4 * TB : -(1 << 30);
+    const int jp0 = max(4 * TB + kHalo + 1, max(jsrc, rec_j1) + 1);
     const bool unit_x = ex0 >= s.unit_x0 && ex0 + EX <= s.unit_x1;
     const int ju0 = max(jp0, s.unit_z0 + 4 * TB), ju1 = min(s.unit_z1 - (kQ - 1) + kHalo, Nz + kGuard - kQ - 1);
     auto group = [&](auto unit, const int j) {

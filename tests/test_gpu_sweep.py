@@ -262,3 +262,65 @@ def test_recompute_on_runs_of_plain_steps_equals_the_tiled_gradient(tuning):
     b = gpu_gradient(g, v, src, rec, wl, resid, ckpt=17)
     assert np.abs(b[0]).max() > 0
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("tuning", WIDE, ids=["s%dz%db%d" % (t["tile_x"], t["tile_z"], t["time_block"]) for t in WIDE])
+@pytest.mark.parametrize("every", [1, 3])
+def test_receivers_down_a_line_and_sources_beside_the_strips_edges(tuning, every):
+    """Receivers down a vertical line (every row of one strip), down a slanted
+    one and on one row all along, more of them than a workgroup has threads;
+    sources on both sides of a strip's edge and just outside its loaded columns,
+    shallow, in a middle and in the last segment.  Gathers and snapshots equal the
+    tiled kernel's bit for bit."""
+    nz, nx, h, nt = 181, 700, 10.0, 64
+    g = Geometry(nz=nz, nx=nx, dz=h, dx=h, dt=8e-4, nt=nt, nbl=20, vmax_hint=4500.0, rec_every=every, snap_every=21,
+                 snap_count=4)
+    v = synth.field_slice(14, nz, nx)
+    edge = tuning["tile_x"] - 8 * tuning["time_block"] - 20      # first output column of the second strip, unpadded
+    halo = 4 * tuning["time_block"]
+    src = np.array([[10.0, (edge - 0.5) * h], [905.0, edge * h], [1790.0, (edge - halo - 0.5) * h],
+                    [1500.0, (edge + halo) * h]])
+    z = np.arange(nz - 1) * h + 4.0
+    rec = np.concatenate([np.stack([z, np.full(nz - 1, 1503.0)], 1), np.stack([z, 200.0 + 3.1 * z], 1),
+                          np.stack([np.full(nx, 600.0), np.arange(nx) * h], 1)])
+    wl = np.stack([oracle.ricker(25.0, g.dt, nt, t0=0.02)] * len(src))
+    a, b = run(g, v, src, rec, wl, tuning), run(g, v, src, rec, wl, TILED)
+    assert all(np.abs(b[1][k]).max() > 0 for k in range(len(src))) and np.abs(b[0]).max() > 0
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+def test_deep_sources_and_vertical_receiver_lines_stay_cheap():
+    """Sources near the bottom and receivers down a vertical line against both
+    at the surface: a source of another strip or segment costs nothing (1.44
+    times the surface's time when it kept the whole shot in the general form),
+    and a line's entries are looked at once a step (5.7 times when once for
+    every level)."""
+    import torch
+    nz, nx, h, nt, nshot = 620, 1001, 10.0, 101, 16
+    g = Geometry(nz=nz, nx=nx, dz=h, dx=h, dt=8e-4, nt=nt, nbl=40, vmax_hint=4500.0)
+    plan, v = Plan(g), torch.from_numpy(synth.field_slice(3, nz, nx)).cuda()
+    wl = torch.from_numpy(np.ascontiguousarray(oracle.ricker(12.0, g.dt, nt), np.float32)).cuda()
+    xs = np.linspace(0.1, 0.9, nshot) * (nx - 1) * h
+    surface = np.stack([np.full(nx, h), np.arange(nx) * h], 1)
+    line = np.stack([np.arange(nz) * h, np.full(nz, 5203.0)], 1)
+
+    def fastest(depth, rec, z, tb):
+        plan.set_tuning(variant=3, tile_x=256, tile_z=z, time_block=tb)
+        shots = Shots(np.stack([np.full(nshot, depth), xs], 1), rec, wl)
+        gathers = torch.empty((nshot, g.nrow, len(rec)), device="cuda")
+        ws = torch.empty(sgwave.sg_forward_workspace_size(plan, nshot, len(rec)), dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            sgwave.sg_forward(plan, v, shots, gathers, None, ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    top, deep = fastest(10.0, surface, 160, 5), fastest(0.92 * (nz - 1) * h, surface, 160, 5)
+    whole, vertical = fastest(10.0, surface, 0, 5), fastest(10.0, line, 0, 5)
+    print("segments %.2f, deep sources %.2f; strips %.2f, vertical line %.2f ms" % (top, deep, whole, vertical), flush=True)
+    assert deep <= 1.3 * top
+    assert vertical <= 4.0 * whole
