@@ -211,13 +211,6 @@ __global__ void __launch_bounds__(kSaltThreads) k_field_bounds(Box b, int ny, in
     lohi[(int64_t)lz * b.bx + lx] = make_float2(lo, hi);
 }
 
-// t^2 (1 + margin), kept finite: a search ends once its best value, which is
-// infinite until it meets a feature, is below its limit.
-__device__ inline double squared_limit(double t, double margin)
-{
-    return fmin(t * t * (1.0 + margin), 1.7976931348623157e308);
-}
-
 // best[i] <- min over k >= k0 of f(i - k) + (w k)^2, f(i + k) + (w k)^2 and
 // itself, i = 0 .. N-1, for f >= 0: outward in steps of four cells, until for
 // every i (w k)^2 exceeds best[i] or lim[i], or best[i] is no more than
@@ -320,7 +313,7 @@ __global__ void __launch_bounds__(kSaltThreads) k_dist_z(Box r, Box b, double dz
         const double t0 = a_rbar * (double)lh.x, t1 = a_rbar * (double)lh.y;
         const double cap = fmax(inner ? fmax(-t0, -t1) : fmax(t0, t1), 0.0);
         best[i] = f(i);
-        lim[i] = z0 + i < zend ? squared_limit(cap, 1e-9) : -1.0;
+        lim[i] = z0 + i < zend ? cap * cap * (1.0 + 1e-9) : -1.0;   // (infinite: nothing is cut off)
     }
     const int k0 = z0 + kOut - 1 < zlo ? zlo - (z0 + kOut - 1) : (z0 > zhi ? z0 - zhi : 1);
     search(best, lim, 0.0, dz, k0, max(zhi - z0, z0 + kOut - 1 - zlo), f);
@@ -367,8 +360,10 @@ __global__ void __launch_bounds__(kSaltThreads) k_dist_y(Box r, Box b, int ny, i
         auto in = [&](int i) { return (inside[i] >> lane & 1) != 0; };
         // a squared distance from (1 + 1e-12) t^2 is above the threshold, one up to (1 - 1.5e-12) t^2 below it
         const double enough = 1.0 - 2.5e-12;
-        // (a t whose square overflows, or an infinite one, is beyond any finite distance)
-        auto limit = [&](int i, bool wanted) { return wanted && y0 + i < yend ? squared_limit(t(i), 1e-12) : -1.0; };
+        // (kept finite where t^2 overflows: a best value is infinite until a feature is met, and must not pass for decided)
+        auto limit = [&](int i, bool wanted) {
+            return wanted && y0 + i < yend ? fmin(t(i) * t(i) * (1.0 + 1e-12), 1.7976931348623157e308) : -1.0;
+        };
         double best[kOut], lim[kOut];
         const double *go = gout + (int64_t)lz * r.by * b.bx + (ix - b.x0);
         auto fo = [&](int i) {
