@@ -19,7 +19,9 @@
 //    the decision it is for is made: phi' = d_in - d_out + a rbar xi > 0
 //    needs d_out only where a rbar xi > 0 and only up to that, d_in only where
 //    a rbar xi < 0 and only up to its negative (k_field_bounds: the extremes of
-//    xi over the rows y, for the pass along z).  k_dist_y sets K.  A body
+//    xi over the rows y, for the pass along z).  k_dist_y sets K.  Where a body
+//    reaches far, k_envelope_z takes k_dist_z's place: the same distances from
+//    the lower envelope of the parabolas, linear in a line's length.  A body
 //    covering no voxel gives d_out = infinity everywhere (phi' = -inf), one
 //    covering all gives d_in = infinity (phi' = +inf): no special cases;
 //  * k_morph x4: opening then closing with the 6-neighbour cross, a voxel
@@ -147,13 +149,15 @@ __global__ void __launch_bounds__(kSaltThreads) k_raster(Box b, double dz, doubl
 // Along x, one wave per row (z, y) of box r: k[row][x - x0], x over [x0, x0 +
 // bx), = cells to the nearest voxel of the row inside r that is a feature (set
 // in `bits`, the raster over r, or not set when `outside`), -1 if the row has
-// none.  The words of r's part are walked upwards with the last feature before
-// the word and the first one after it (a second index into the row).
+// none; rows in [z][y], or with `by_y` in [y][z].  The words of r's part are
+// walked upwards with the last feature before the word and the first one after
+// it (a second index into the row).
 __global__ void __launch_bounds__(kSaltThreads) k_dist_x(Box r, int x0, int bx, const uint64_t *__restrict__ bits,
-                                                         int outside, int32_t *__restrict__ k)
+                                                         int outside, bool by_y, int32_t *__restrict__ k)
 {
     const int64_t row = wave_index();
     if (row >= (int64_t)r.bz * r.by) return;
+    int32_t *kr = k + (by_y ? row % r.by * r.bz + row / r.by : row) * bx;
     const int lane = threadIdx.x & 63;
     const int w0 = r.x0 / 64, w1 = (r.x0 + r.bx - 1) / 64;
     const uint64_t *rw = bits + row * box_words(r) - w0;
@@ -181,7 +185,7 @@ __global__ void __launch_bounds__(kSaltThreads) k_dist_x(Box r, int x0, int bx, 
         int d = -1;
         if (l >= 0) d = x - l;
         if (n >= 0 && (d < 0 || n - x < d)) d = n - x;
-        if (x >= x0 && x < x0 + bx) k[row * bx + (x - x0)] = d;
+        if (x >= x0 && x < x0 + bx) kr[x - x0] = d;
         if (f) last = w * 64 + 63 - __clzll((long long)f);
     }
 }
@@ -410,6 +414,108 @@ __global__ void __launch_bounds__(kSaltThreads) k_dist_y(Box r, Box b, int ny, i
     }
 }
 
+// g[p] = min over q of (w (p0 + p - q))^2 + f(q), p = 0 .. m-1, q = 0 .. n-1:
+// the lower envelope of the parabolas rooted at the finite samples.  v holds
+// the envelope's roots (stride vs), g's stride is gs.  The top two roots also
+// live in registers; where neighbouring parabolas meet is computed again when
+// it is needed (kept in memory, it would be the largest array).  f is read four
+// samples ahead.
+template <class F>
+__device__ __forceinline__ void envelope(int n, int p0, int m, double w, F f, int32_t *v, int64_t vs, double *g, int64_t gs)
+{
+    const double w2 = w * w;
+    auto height = [&](int q, double fq) { return fq + w2 * ((double)q * q); };
+    // abscissa where the parabola of root b starts to lie below that of a < b
+    auto meet = [&](int a, double ha, int b, double hb) { return (hb - ha) / (2.0 * w2 * (double)(b - a)); };
+    int k = -1;                    // index of the last parabola of the envelope
+    int vk = 0, vl = 0;            // its root, and that of the one before
+    double hk = 0.0, hl = 0.0;     // their heights
+    double zk = 0.0;               // where it starts
+    double f0 = f(0), f1 = n > 1 ? f(1) : 0.0, f2 = n > 2 ? f(2) : 0.0, f3 = n > 3 ? f(3) : 0.0;
+    for (int q = 0; q < n; ++q) {
+        const double fq = f0;
+        f0 = f1;
+        f1 = f2;
+        f2 = f3;
+        f3 = q + 4 < n ? f(q + 4) : 0.0;
+        if (!(fq < inf_d())) continue;
+        const double hq = height(q, fq);
+        double s = 0.0;
+        while (k >= 0) {
+            s = meet(vk, hk, q, hq);
+            if (k == 0 || s > zk) break;
+            --k;
+            vk = vl;
+            hk = hl;
+            if (k > 0) {
+                vl = v[(k - 1) * vs];
+                hl = height(vl, f(vl));
+                zk = meet(vl, hl, vk, hk);
+            }
+        }
+        if (++k > 0) {
+            vl = vk;
+            hl = hk;
+            zk = s;
+        }
+        vk = q;
+        hk = hq;
+        v[k * vs] = q;
+    }
+    if (k < 0) {
+        for (int p = 0; p < m; ++p) g[p * gs] = inf_d();
+        return;
+    }
+    int j = 0, vj = v[0], vn = 0;
+    double fj = f(vj), fn = 0.0, zn = inf_d();   // (zn: where parabola j + 1 starts)
+    auto look_ahead = [&]() {
+        zn = inf_d();
+        if (j < k) {
+            vn = v[(j + 1) * vs];
+            fn = f(vn);
+            zn = meet(vj, height(vj, fj), vn, height(vn, fn));
+        }
+    };
+    look_ahead();
+    for (int p = 0; p < m; ++p) {
+        const double at = (double)(p0 + p);
+        while (zn < at) {
+            ++j;
+            vj = vn;
+            fj = fn;
+            look_ahead();
+        }
+        const double d = w * (at - (double)vj);
+        g[p * gs] = d * d + fj;
+    }
+}
+
+// The pass along z where k_dist_z's searches would go far: the same distances,
+// none of them cut off, one thread per line of box r's rows y, the transforms of
+// d_in (on r) and d_out (on box `outer`, from r) side by side (blockIdx.y).  The
+// x distances k come with rows in [y][z], so that a line's samples lie close.
+struct EnvelopeSide {
+    const int32_t *k;
+    double *g;
+    int32_t *v;   // room for the roots
+};
+__global__ void __launch_bounds__(kSaltThreads) k_envelope_z(Box r, Box outer, double dz, double dx, EnvelopeSide in,
+                                                             EnvelopeSide out)
+{
+    const Box b = blockIdx.y == 0 ? r : outer;
+    const EnvelopeSide S = blockIdx.y == 0 ? in : out;
+    const int64_t l = (int64_t)blockIdx.x * kSaltThreads + threadIdx.x;
+    if (l >= (int64_t)r.by * b.bx) return;
+    const int ly = (int)(l / b.bx), lx = (int)(l - (int64_t)ly * b.bx);
+    const int64_t at = (int64_t)ly * r.bz * b.bx + lx;
+    auto f = [&](int q) {
+        const int32_t c = S.k[at + (int64_t)q * b.bx];
+        const double d = dx * (double)c;
+        return c < 0 ? inf_d() : d * d;
+    };
+    envelope(r.bz, b.z0 - r.z0, b.bz, dz, f, S.v + at, b.bx, S.g + (int64_t)ly * b.bx + lx, (int64_t)r.by * b.bx);
+}
+
 __global__ void __launch_bounds__(kSaltThreads) k_fill_u32(int64_t n, unsigned val, unsigned *p)
 {
     for (int64_t q = (int64_t)blockIdx.x * kSaltThreads + threadIdx.x; q < n; q += (int64_t)gridDim.x * kSaltThreads)
@@ -630,6 +736,23 @@ __global__ void __launch_bounds__(kSaltThreads) k_salt_write(int64_t nrow, int n
     }
 }
 
+// The pass along z searches while no search can go farther than kFarSearch
+// cells (the largest |a rbar xi|, or the box's planes), and takes the envelopes
+// beyond: a search's cost grows with its length, an envelope's does not.  One
+// body with a smooth field, both transforms: 619 x 1000 x 1000 voxels, radii 155
+// cells, search up to 85 cells 1.07 ms and envelopes 1.48, 170 2.10 and 1.65, 283
+// 3.52 and 1.75, 567 11.3 and 1.93; radii 413, 227 cells 24.8 and 10.5; 300 x 400 x
+// 400, radii 83, 118 cells 0.34 and 0.49, 235 0.60 and 0.48.  An envelope is one
+// thread per line, so below kFewLines lines, which leave the chip idle, the
+// searches may be longer in proportion: 4000 x 200 x 100 (20000 lines), 520 cells
+// 2.9 and 3.0; 619 x 1 x 1000, 124 cells 0.06 and 0.80.
+// (The pass along y ends at the decision, whatever the limit: 567 cells in the
+// full volume 11.5 ms and 9.3 by envelopes, 378 with radii of 413 11.9 and 22.2,
+// 880 in 20 x 2000 x 600 voxels 0.5 and 2.5.  Envelopes in both passes were faster
+// in all on very long lines under fields of several times the radii: 200 x 10000 x
+// 100 at amplitude 3 27.0 ms against 30.8, 400 x 1500 x 1000 50.3 against 50.6.)
+constexpr double kFarSearch = 160.0, kFewLines = 80000.0;
+
 // The workspace holds six arrays of 8 bytes and two of 4 bytes per voxel, and
 // two of a byte.  Used: the two transforms' x distances and their distances
 // over x and z (d_in, d_out, f), the sets K and its scratch (words; as many as
@@ -742,22 +865,38 @@ hipError_t launch_salt_sdt(const float *v, int nz, int ny, int nx, double dz, do
                       1e-6 * rmax + tol / std::sqrt(cyy)};
         const double a_rbar = amplitude * rbar;
         const float *xi = grf + (int64_t)i * n;
-        float2 *lohi = (float2 *)W.T;
-        hipLaunchKernelGGL(k_field_bounds, dim3(wave_blocks((int64_t)((bo.bx + 63) / 64) * bo.bz)), blk, 0, st, bo, ny,
-                           nx, xi, lohi);
         hipLaunchKernelGGL(k_raster, dim3(wave_blocks((int64_t)bi.bz * bi.by * box_words(bi))), blk, 0, st, bi, dz, dy,
                            dx, B, W.raster);
+        auto dist_x = [&](const Box &b, int outside, bool by_y, void *k) {
+            hipLaunchKernelGGL(k_dist_x, dim3(wave_blocks((int64_t)bi.bz * bi.by)), blk, 0, st, bi, b.x0, b.bx,
+                               (const uint64_t *)W.raster, outside, by_y, (int32_t *)k);
+        };
         // d_in: distance to the nearest voxel outside, on bi; d_out: to the nearest inside, on the planes and
         // columns of bo and (before the last pass) the rows y of bi, which hold the whole body
-        auto transform = [&](const Box &b, int inner, int32_t *k, double *g) {
-            hipLaunchKernelGGL(k_dist_x, dim3(wave_blocks((int64_t)bi.bz * bi.by)), blk, 0, st, bi, b.x0, b.bx,
-                               (const uint64_t *)W.raster, inner, k);
-            const int64_t waves = (int64_t)((b.bx + 63) / 64) * bi.by * ((b.bz + kOutZ - 1) / kOutZ);
-            hipLaunchKernelGGL(k_dist_z, dim3(wave_blocks(waves)), blk, 0, st, bi, b, dz, dy, dx, S, inner, a_rbar, bo,
-                               (const float2 *)lohi, (const int32_t *)k, g);
-        };
-        transform(bi, 1, (int32_t *)W.din, W.f[0]);
-        transform(bo, 0, (int32_t *)W.dout, W.f[1]);
+        const double reach_in = std::max(0.0, amplitude >= 0 ? amplitude * rbar * lo : -amplitude * rbar * hi);
+        const double far = std::max(std::min(reach / dz, (double)bo.bz), std::min(reach_in / dz, (double)bi.bz));
+        const double lines = (double)bi.by * bo.bx;
+        if (far > kFarSearch * std::max(kFewLines / lines, 1.0)) {
+            dist_x(bi, 1, true, W.din);
+            dist_x(bo, 0, true, W.dout);
+            // (the roots lie behind the x distances: 8 bytes a voxel hold both)
+            const EnvelopeSide in{(const int32_t *)W.din, W.f[0], (int32_t *)W.din + n};
+            const EnvelopeSide out{(const int32_t *)W.dout, W.f[1], (int32_t *)W.dout + n};
+            hipLaunchKernelGGL(k_envelope_z, dim3(blocks_for((int64_t)bi.by * bo.bx), 2), blk, 0, st, bi, bo, dz, dx, in,
+                               out);
+        } else {
+            float2 *lohi = (float2 *)W.T;
+            hipLaunchKernelGGL(k_field_bounds, dim3(wave_blocks((int64_t)((bo.bx + 63) / 64) * bo.bz)), blk, 0, st, bo,
+                               ny, nx, xi, lohi);
+            auto transform = [&](const Box &b, int inner, int32_t *k, double *g) {
+                dist_x(b, inner, false, k);
+                const int64_t waves = (int64_t)((b.bx + 63) / 64) * bi.by * ((b.bz + kOutZ - 1) / kOutZ);
+                hipLaunchKernelGGL(k_dist_z, dim3(wave_blocks(waves)), blk, 0, st, bi, b, dz, dy, dx, S, inner, a_rbar,
+                                   bo, (const float2 *)lohi, (const int32_t *)k, g);
+            };
+            transform(bi, 1, (int32_t *)W.din, W.f[0]);
+            transform(bo, 0, (int32_t *)W.dout, W.f[1]);
+        }
         const int64_t waves = (int64_t)box_words(bo) * bo.bz * ((bo.by + kOutY - 1) / kOutY);
         hipLaunchKernelGGL(k_dist_y, dim3(wave_blocks(waves)), blk, 0, st, bi, bo, ny, nx, dy,
                            (const uint64_t *)W.raster, (const double *)W.f[0], (const double *)W.f[1], xi, a_rbar, W.K);
