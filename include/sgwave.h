@@ -147,8 +147,9 @@ typedef struct {
  * All zeros ask for the library's default: 128x64 and the time blocks above
  * (what sg_plan_get_tuning reports), but a single call small enough to run in
  * finer tiles or longer time blocks with every tile resident at once does so,
- * with the same gathers and snapshots.  sg_plan_set_tuning rejects
- * shapes that are not built with SG_EUNSUPPORTED.
+ * with the same gathers and snapshots.  (Setting the reported tuning names it,
+ * for such calls too; all zeros return to the default.)  sg_plan_set_tuning
+ * rejects shapes that are not built with SG_EUNSUPPORTED.
  */
 typedef struct {
     int32_t variant;
@@ -201,7 +202,9 @@ sg_status sg_plan_padded_shape(const sg_plan *p, int32_t *Nz, int32_t *Nx);
  * Returns SG_EINVAL for values outside the documented ranges. */
 sg_status sg_plan_set_tuning(sg_plan *p, const sg_tuning *t);
 
-/* Tuning the plan will use for nshot shots (after defaults are resolved). */
+/* Tuning the plan will use for nshot shots (after defaults are resolved; of
+ * the default's own choice for small calls it reports the 128x64 tiling, as
+ * described with sg_tuning). */
 sg_status sg_plan_get_tuning(const sg_plan *p, int32_t nshot, sg_tuning *t);
 
 /*
@@ -210,8 +213,11 @@ sg_status sg_plan_get_tuning(const sg_plan *p, int32_t nshot, sg_tuning *t);
  * time blocks 2..6, whole height or segments of 160, 224 or 320 rows) where
  * dz == dx, on this call's real shape -- trial_levels (>= 8) levels of the
  * time-stepping launches for `shots` on `vp`, after one untimed pass -- and
- * keeps the fastest as the plan's tuning (also returned in *best).  Uses the
- * workspace of sg_forward (no outputs are written).  Synchronises the stream.
+ * keeps the fastest as the plan's tuning (also returned in *best).  Where the
+ * library's default runs such a small call in a tiling of its own, that is
+ * timed too: if it is the fastest, the plan returns to the default and *best is
+ * all zeros.  Uses the workspace of sg_forward (no outputs are written).
+ * Synchronises the stream.
  */
 sg_status sg_autotune(sg_plan *p, const float *vp, const sg_shots *shots, int32_t trial_levels, void *ws,
                       size_t ws_bytes, void *stream, sg_tuning *best);

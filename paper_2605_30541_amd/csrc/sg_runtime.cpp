@@ -1723,10 +1723,18 @@ sg_status sg_autotune(sg_plan *p, const float *vp, const sg_shots *shots, int32_
     const int levels = std::min(trial_levels, p->g.nt - 1);
     double best_ms = 1e300;
     sg_tuning chosen{};
-    for (const sg_tuning &t : tuning_candidates(p)) {
+    // the default's own tiling of this call, which no tuning names, stands for
+    // "all zeros"; where it has none, the default is among the candidates
+    std::vector<sg_tuning> candidates = tuning_candidates(p);
+    candidates.insert(candidates.begin(), sg_tuning{});
+    for (const sg_tuning &candidate : candidates) {
         int config = -1;
         sg::Tiling T{};
-        if (tiling_for(p, t, &config, &T) != SG_OK) continue;
+        sg_tuning t = candidate;
+        if (t.variant == 0 ? !one_round_tiling(p, shots->nshot, false, &t, &config, &T)
+                           : tiling_for(p, t, &config, &T) != SG_OK)
+            continue;
+        if (t.variant == 0) t.variant = 2;
         if ((rc = upload_tables(p, c.L, w, shots, &T, st)) != SG_OK) break;
         // a trial: no outputs recorded, fields zeroed, the same levels for every candidate
         sg::SliceDesc s = describe(p, c.L, w, shots, nullptr, nullptr);
@@ -1754,7 +1762,7 @@ sg_status sg_autotune(sg_plan *p, const float *vp, const sg_shots *shots, int32_
         }
         if (ms < best_ms) {
             best_ms = ms;
-            chosen = t;
+            chosen = candidate;
         }
     }
     (void)hipEventDestroy(e0);

@@ -108,3 +108,41 @@ def test_gradient_with_few_and_many_nodes_per_tile(nrec, tuning):
     got, _ = gpu_gradient(g, v, src, rec, wl, resid, ckpt=12, tuning=tuning)
     assert np.linalg.norm(ref) > 0
     assert rel_l2(got, ref) <= 1e-4
+
+
+@pytest.mark.parametrize("nz,nx,nshot", [(64, 128, 1), (30, 40, 2), (200, 300, 1), (620, 1001, 4)])
+def test_autotuned_calls_are_no_slower_than_the_default(nz, nx, nshot):
+    """The autotuner also times the tiling that the default takes for a small
+    call; when that is the fastest it reports all zeros, which set the default.
+    Gathers stay the same bit for bit."""
+    import torch
+    g = Geometry(nz=nz, nx=nx, dz=10.0, dx=10.0, dt=1e-3, nt=241, nbl=20, vmax_hint=3000.0)
+    v = torch.full((nz, nx), 2500.0, device="cuda")
+    wl = torch.from_numpy(oracle.ricker(30.0, g.dt, g.nt).astype(np.float32)).cuda()
+    shots = Shots(np.full((nshot, 2), 100.0), np.stack([np.full(nx, 10.0), np.arange(nx) * 10.0], 1), wl[None])
+    plan = Plan(g)
+    ws = torch.empty(sgwave.sg_forward_workspace_size(plan, nshot, nx), dtype=torch.uint8, device="cuda")
+
+    def run_once(gathers):
+        sgwave.sg_forward(plan, v, shots, gathers, None, ws)
+
+    def fastest():
+        gathers, times = torch.empty((nshot, g.nrow, nx), device="cuda"), []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            run_once(gathers)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times), gathers
+
+    default, ref = fastest()
+    best = sgwave.sg_autotune(plan, v, shots, 64, ws)
+    tuned, got = fastest()
+    print("%d x %d, %d shots: default %.3f ms, autotuned %.3f ms %s" % (nz, nx, nshot, default, tuned, best), flush=True)
+    assert tuned <= 1.1 * default
+    assert torch.equal(got, ref)
+    plan.set_tuning(**best)
+    if not any(best.values()):
+        assert plan.get_tuning(nshot)["time_block"] == 4 and fastest()[0] <= 1.1 * default
