@@ -778,6 +778,17 @@ sg_status setup_call(sg_plan *p, const float *vp, const sg_shots *shots, void *w
     return SG_OK;
 }
 
+// Segments of a batch's items that differ in height by more than a tenth: the
+// column sweep's blocks are then dealt out item by item (launch_sweep_batch), as
+// the XCDs that would get the shorter ones idle at the end of each launch.  Time
+// in launch order over time dealt out, 8 or 20 shots an item, four tilings: 8
+// slices of 459 to 629 rows 1.00 to 1.11, 2 of 400 and 620 1.00 to 1.08, 4 of 500 to
+// 620 0.98 to 1.02; equal slices, whose tiles stay in one L2, 8 of 550 rows 0.96 to
+// 1.01, 4 of 600 0.96 to 1.05.  In a gradient, where the adjoint takes most of the
+// time, 1.00 to 1.04, 1.00 to 1.02 and 0.99 to 1.01: batches of at least one item
+// per XCD only.
+bool uneven_segments(int32_t least, int32_t most) { return 10 * (int64_t)most > 11 * (int64_t)least; }
+
 // Pinned staging of the per-call device headers of batched calls (item
 // tables), used in turn like a plan's table slots; a slot grows (one pinned
 // allocation) when a larger batch arrives.
@@ -1593,6 +1604,12 @@ sg_status batch_forward_impl(const sg_batch_item *items, int32_t nitems, const s
     // the time-stepping launches (one per time block over the whole batch),
     // replayed from a captured graph unless the caller is capturing already
     const int config = cs[0].config, tb = t.time_block, sweep_nw = cs[0].T.sweep_nw;
+    int32_t least = cs[0].T.tz, most = least;
+    for (int i = 1; i < nitems; ++i) {
+        least = std::min(least, cs[i].T.tz);
+        most = std::max(most, cs[i].T.tz);
+    }
+    const bool deal = uneven_segments(least, most);
     // the isotropic kernel form needs dz == dx on every item
     bool iso = true;
     for (int i = 0; i < nitems; ++i)
@@ -1621,7 +1638,7 @@ sg_status batch_forward_impl(const sg_batch_item *items, int32_t nitems, const s
         for (int n = 0; n < nlast;) {
             const int k = std::min(std::min(tb, nlast - n), next_cut(n) - n);
             if (sweep_nw > 0)
-                SG_HIP(sg::launch_sweep_batch(dev_items, nitems, (int)total_blocks, n, k, {pair}, sweep_nw, true, s2));
+                SG_HIP(sg::launch_sweep_batch(dev_items, nitems, (int)total_blocks, n, k, {pair}, sweep_nw, deal, s2));
             else
                 SG_HIP(sg::launch_step_tiled_batch(dev_items, nitems, (int)total_blocks, n, k, {pair}, config, iso, s2));
             pair ^= 1;
@@ -1942,13 +1959,19 @@ sg_status sg_batch_adjoint_gradient(const sg_batch_grad_item *items, int32_t nit
         // recompute (four slices of 20 shots, four segments of 50 levels: 92.6
         // -> 87.9 ms).
         const int nseg = Ls[0].nseg;
+        int32_t least = INT32_MAX, most = 0;
+        for (int i : act) {
+            least = std::min(least, Tf[i].tz);
+            most = std::max(most, Tf[i].tz);
+        }
+        const bool deal = na >= 8 && uneven_segments(least, most);
         auto advance = [&](int n, int k, sg::LevelPair lv, int ring_of) {
             if (ring_of < 0)
-                return sweep_fwd ? sg::launch_sweep_batch(dev_fwd, na, start, n, k, lv, Tf[0].sweep_nw, false, st)
+                return sweep_fwd ? sg::launch_sweep_batch(dev_fwd, na, start, n, k, lv, Tf[0].sweep_nw, deal, st)
                                  : sg::launch_step_tiled_batch(dev_fwd, na, start, n, k, lv, config, iso, st);
             sg::BatchItem *const dev = dev_fwd_r[ring_of & 1];
             return sweep_fwd
-                       ? sg::launch_sweep_batch(dev, na, start, n, k, lv, Tf[0].sweep_nw, false, st, true, ring_of * C)
+                       ? sg::launch_sweep_batch(dev, na, start, n, k, lv, Tf[0].sweep_nw, deal, st, true, ring_of * C)
                        : sg::launch_ring_tiled_batch(dev, na, start, n, k, lv, config, iso, ring_of * C, st);
         };
         int pair = 0;

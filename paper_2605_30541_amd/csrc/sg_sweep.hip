@@ -431,8 +431,7 @@ __global__ void __launch_bounds__(64 * NW) SG_SWEEP_OCCUPANCY k_sweep_batch(cons
     // eighth of every item's.  The first gives an XCD one or two items, whose
     // segments may be higher than the others': eight slices of 459 to 629 rows
     // (153 to 210 a segment) left the shorter ones' XCDs idle at the end of each
-    // launch, 87.8 ms against 82.1.  The gradient's batches keep the first (four
-    // slices of 550 to 633 rows: 93.8 ms against 94.5 dealt out).
+    // launch, 87.8 ms against 82.1.
     const int b = deal ? (int)blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
     int it = 0;
     if (nitems > 1) {

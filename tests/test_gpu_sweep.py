@@ -324,3 +324,38 @@ def test_deep_sources_and_vertical_receiver_lines_stay_cheap():
     print("segments %.2f, deep sources %.2f; strips %.2f, vertical line %.2f ms" % (top, deep, whole, vertical), flush=True)
     assert deep <= 1.3 * top
     assert vertical <= 4.0 * whole
+
+
+@pytest.mark.parametrize("nzs", [(60, 95, 70, 120, 64, 88, 101, 73, 110), (77,) * 8, (60, 120)],
+                         ids=["nine-uneven", "eight-equal", "two-uneven"])
+@pytest.mark.parametrize("tuning", [dict(variant=3, tile_x=128, tile_z=48, time_block=3),
+                                    dict(variant=3, tile_x=256, tile_z=0, time_block=4)], ids=["s128z48b3", "s256z0b4"])
+def test_batches_dealt_out_by_item_or_not_equal_single_calls(nzs, tuning):
+    """Batches whose segments differ in height and batches of equal ones, fewer
+    items than XCDs and more: gathers and gradients (three segments of levels:
+    two from the forward, one recomputed) equal the single calls' bit for bit."""
+    import torch
+    from test_gpu_gradient import gpu_gradient
+    nt, ckpt, h = 71, 25, 10.0
+    items, grads, single = [], [], []
+    for i, nz in enumerate(nzs):
+        nx, nshot = 90 + 37 * (i % 4), 1 + i % 3
+        g = Geometry(nz=nz, nx=nx, dz=h, dx=h, dt=8e-4, nt=nt, nbl=14, vmax_hint=4500.0)
+        v = synth.field_slice(40 + i, nz, nx)
+        src = synth.shot_line(nshot, 0.2 * (nx - 1) * h, 0.8 * (nx - 1) * h, depth=12.5)
+        rec = synth.surface_receivers(nx, h)
+        wl = oracle.ricker(25.0, g.dt, nt, t0=0.02)
+        resid = np.random.default_rng(i).standard_normal((nshot, g.nrow, nx)).astype(np.float32)
+        single.append(gpu_gradient(g, v, src, rec, wl, resid, ckpt=ckpt, tuning=tuning))
+        vp = torch.from_numpy(np.ascontiguousarray(v, np.float32)).cuda()
+        shots = Shots(src, rec, torch.from_numpy(np.atleast_2d(wl).astype(np.float32)).cuda())
+        items.append((Plan(g), vp, shots))
+        grads.append((items[-1][0], vp, shots, torch.from_numpy(resid).cuda(), torch.empty_like(vp)))
+    out = sgwave.batch_forward(items, tuning)
+    ws = torch.empty(sgwave.sg_batch_grad_workspace_size(grads, ckpt, 0), dtype=torch.uint8, device="cuda")
+    sgwave.sg_batch_adjoint_gradient(grads, ws, ckpt, 0, tuning=tuning)
+    torch.cuda.synchronize()
+    for (gathers, _), (_, _, _, _, grad), (one, d) in zip(out, grads, single):
+        assert np.abs(one).max() > 0 and np.abs(d).max() > 0
+        assert np.array_equal(gathers.cpu().numpy(), d)
+        assert np.array_equal(grad.cpu().numpy(), one)
