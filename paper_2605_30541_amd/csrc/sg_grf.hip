@@ -20,6 +20,7 @@
 // transposed (six passes of 16 GB in 32-byte pieces), 9.9 ms in this form.
 #include "sg_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace sg {
@@ -45,15 +46,25 @@ __device__ inline double wavenumber2(int i, int n, double l)
 // q^-half_p for q >= 1: log2 q = e + log2 m with q = m 2^e, the
 // product with half_p in FP64, of which only the fraction goes through the
 // FP32 exponential.  (FP32 throughout, the rounding of log2 q ~ 14 alone
-// moved the field by 1e-7 of its norm.)  A q beyond FP64 (infinite, from
-// lengths past 1e153 cells) gives 0, or 1 where half_p is 0; exponents past
-// 1000, infinite ones among them, give 0.
+// moved the field by 1e-7 of its norm.)  q and half_p log2 q must be finite:
+// spectrum() sees to it.
 __device__ inline float spectral_amp(double q, double half_p)
 {
     int e;
     const float m = (float)frexp(q, &e);   // in [1/2, 1)
-    const double s = half_p > 0.0 ? fmin(half_p * ((double)e + (double)log2f(m)), 1000.0) : 0.0, n = rint(s);
-    return ldexpf(exp2f((float)(n - s)), -(int)n);
+    const double s = half_p * ((double)e + (double)log2f(m)), n = rint(s);
+    return ldexpf(exp2f((float)(n - s)), -(int)fmin(n, 1000.0));
+}
+
+// Lengths and exponents so large that (k l)^2 or the power would leave FP64 are
+// taken smaller: the factor is then at most (1e147)^-p on that axis.
+// (Clamped in the kernel, per value, the z pass lost a wave per SIMD: 9.8 -> 11.1
+// ms for a 619 x 1000 x 1000 field.)
+Spectrum spectrum(const int P[3], double lz, double ly, double lx, double p)
+{
+    const double most = 1e150;
+    return Spectrum{P[0], P[1], P[2], std::min(lz, most), std::min(ly, most), std::min(lx, most),
+                    std::min(0.5 * p, 1e300)};
 }
 
 // Where the half spectrum lives: row (z, y) of Px/2 + 1 values starts at z *
@@ -536,7 +547,7 @@ hipError_t launch_grf(const float *noise, int nz, int ny, int nx, double lz, dou
     int P[3];
     grf_grid(nz, ny, nx, P);
     const HalfGrid G = half_grid(P);
-    const Spectrum S{P[0], P[1], P[2], lz, ly, lx, 0.5 * p};
+    const Spectrum S = spectrum(P, lz, ly, lx, p);
     // the half spectrum, the result's statistics and the sums per workgroup of pass 5
     float2 *a = (float2 *)ws;
     const int64_t npair = (int64_t)nz * ((ny + 1) / 2), blocks = (npair + kC - 1) / kC;
