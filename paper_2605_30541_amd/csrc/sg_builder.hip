@@ -735,7 +735,8 @@ __global__ void __launch_bounds__(256) k_simplex3d(const int32_t *__restrict__ p
 // Bound by FP64 vector issue (about 200 operations a voxel with simplex
 // texture).  One thread per whole column, all contacts looked at for every
 // voxel, left two waves per SIMD (LDS) and took 7.17 ms for a 200 x 1000 x
-// 1000 band of 40 beds with simplex noise; this form 1.41 ms.  10 depths of 120
+// 1000 band of 40 beds with simplex noise; this form 1.41 ms (with the
+// inputs of bench.py's band 7.2 and 1.6).  10 depths of 120
 // beds with value noise, whose contacts cross 40 others: 1.97 ms that way, 9.84
 // with one wave sorting each column's by insertion, 1.10 in this form.
 template <bool SIMPLEX, int WAVES>

@@ -825,7 +825,7 @@ __global__ void __launch_bounds__(256) k_init_checkpoints(SliceDesc s, int frame
 // 1681 at a 40-cell sponge), so each edge cell is a wave, its lanes taking the
 // cells in turn and adding up in a fixed tree: one thread per edge cell, and a
 // sum over the shots in each, was a serial chain of 27k dependent additions
-// (2.54 ms for the 620 x 1001 slice with 16 shots; this form 7 us).
+// (2.54 ms for the 620 x 1001 slice with 16 shots; this form 15 us).
 __global__ void __launch_bounds__(256) k_fold_gradient(SliceDesc s, const float *vp, const double *hsum, float dt,
                                                        float *grad, int accumulate, int inner_blocks)
 {
