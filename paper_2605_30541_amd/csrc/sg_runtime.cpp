@@ -1743,7 +1743,7 @@ sg_status sg_autotune(sg_plan *p, const float *vp, const sg_shots *shots, int32_
     // the default's own tiling of this call, which no tuning names, stands for
     // "all zeros"; where it has none, the default is among the candidates
     std::vector<sg_tuning> candidates = tuning_candidates(p);
-    candidates.insert(candidates.begin(), sg_tuning{});
+    candidates.push_back(sg_tuning{});
     for (const sg_tuning &candidate : candidates) {
         int config = -1;
         sg::Tiling T{};
@@ -1777,7 +1777,7 @@ sg_status sg_autotune(sg_plan *p, const float *vp, const sg_shots *shots, int32_
             rc = fail(SG_EHIP, "event timing failed");
             break;
         }
-        if (ms < best_ms) {
+        if (candidate.variant == 0 ? ms <= best_ms : ms < best_ms) {
             best_ms = ms;
             chosen = candidate;
         }
